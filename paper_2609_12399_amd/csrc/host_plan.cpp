@@ -81,6 +81,39 @@ size_t prefill_chunked_workspace_bytes(const Shape& s, int prompt_len) {
   return up(units * nch * per) + up(units * nch * 16 * sizeof(float));
 }
 
+// A scan workgroup holds up to 128 rows of the state (or of a segment's d_k x d_k
+// transition matrix) for the whole segment, one workgroup per compute unit (two
+// at d_k <= 64, by their LDS).  A chunk takes about 4 us there, the launch that
+// chains n segments about 4 + 1.5 (n - 1) us (both measured at 16 heads, d = 128),
+// and every segment but the first also carries its transition matrix, so segments
+// pay only while workgroups are missing: 16 heads x 64 chunks 8 segments, 42 + 13 us
+// (4: 66 + 7; 6: 51 + 10); 64 heads x 32 chunks 2, 75 + 8 (4: 83 + 14); 256 heads none.
+int prefill_segments(const Shape& s, int nch) {
+  if (nch < 8 || s.cus <= 0) return 1;
+  const size_t waves = std::min(s.dv / 16, 8);
+  const size_t gb = s.dv / (16 * waves), ga = s.dk / (16 * waves);
+  const size_t units = size_t(s.R) * s.HV;
+  const size_t slots = size_t(s.cus) * (s.dk <= 64 ? 2 : 1);
+  const size_t room = size_t(nch) * (size_t(kPrefillChunk) * (2 * s.dk + s.dv) * sizeof(float) -
+                                     kPrefillFactorBytes);
+  auto cost = [&](int n, int chunks) {  // in 0.4 us
+    const size_t wgs = units * (gb + size_t(n - 1) * (gb + ga));
+    return 10 * ((wgs + slots - 1) / slots) * size_t(chunks) + (n > 1 ? 10 + 4 * size_t(n - 1) : 0);
+  };
+  int best = 1;
+  size_t best_cost = cost(1, nch);
+  for (int want = 2; want <= nch / 4 && want <= 16; ++want) {
+    const int cps = (nch + want - 1) / want, n = (nch + cps - 1) / cps;
+    // the segments' B (fp32) and A (three bf16 parts) stay inside the workspace
+    if ((size_t(n) * s.dv * 4 + size_t(n - 1) * s.dk * 6) * s.dk > room) continue;
+    if (n > 1 && cost(n, cps) < best_cost) {
+      best_cost = cost(n, cps);
+      best = n;
+    }
+  }
+  return best;
+}
+
 bool select_plan(int R, unsigned N, unsigned W, SelectPlan* plan) {
   *plan = SelectPlan{};
   if (R < 1 || N < 1 || W < 1 || W > N || W > unsigned(kSelectMaxWidth) ||

@@ -49,6 +49,12 @@ bool decode_supported(const Shape& s);
 // Tokens per chunk of the chunked prefill and its workspace size.
 constexpr int kPrefillChunk = 64;  // tokens per chunk
 size_t prefill_chunked_workspace_bytes(const Shape& s, int prompt_len);
+// Bytes of one chunk's factors in that workspace (bf16 keys): the split T' of
+// the chunk (6 x 3 KiB) and its 64 decays.
+constexpr size_t kPrefillFactorBytes = 6 * 3 * 1024 + 64 * 4;
+// Segments that the scan over nch chunks is cut into (bf16 keys; every segment
+// has at least one chunk, 1 for an empty prompt).
+int prefill_segments(const Shape& s, int nch);
 
 // ---- global top-W beam selection ------------------------------------------
 constexpr int kSelectThreads = 512;            // one workgroup

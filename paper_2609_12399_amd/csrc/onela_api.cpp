@@ -269,6 +269,7 @@ onela_status_t onela_prefill_state_chunked(const onela_config_t* cfg, int32_t pr
   if (need > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0))
     return ONELA_EINVAL;
   if (workspace_bytes < need) return ONELA_ECAPACITY;
+  s.cus = device_compute_units();
   const hipError_t e =
       onela::launch_prefill_chunked(s, prompt_len, k, v, alpha, beta, s0_out, workspace,
                                     static_cast<hipStream_t>(stream));

@@ -54,6 +54,17 @@ static void configs() {
                   EXPECT(!s.borrow || (l.k == 0 && l.v == 0 && l.ab == 0));
                   EXPECT(s.delta == (l.d > 0));
                   EXPECT(prefill_chunked_workspace_bytes(s, 0) % 256 == 0);
+                  for (int nch : {0, 1, 7, 8, 9, 31, 64, 129, 1000}) {
+                    Shape g = s;
+                    g.cus = 256;
+                    const int n = prefill_segments(g, nch);
+                    EXPECT(n == 1 || (n > 1 && n <= nch / 4));
+                    // factors, the segments' B (fp32) and A (three bf16 parts)
+                    const size_t units = size_t(s.R) * s.HV;
+                    const size_t seg = n == 1 ? 0 : (size_t(n) * s.dv * 4 + size_t(n - 1) * s.dk * 6) * s.dk;
+                    EXPECT(units * (size_t(nch) * kPrefillFactorBytes + seg) <=
+                           prefill_chunked_workspace_bytes(s, nch * kPrefillChunk));
+                  }
                   EXPECT(prefill_chunked_workspace_bytes(s, 65) >=
                          prefill_chunked_workspace_bytes(s, 64));
                 }

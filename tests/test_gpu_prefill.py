@@ -108,3 +108,22 @@ def test_chunked_matches_sequential_prefill():
     seq = runner.prefill_state(wl.spec, prompt, DEV).cpu().numpy()
     got = run_chunked(wl)
     assert state_err(got, seq.astype(np.float64)) <= TOL
+
+
+# bf16 keys: the scan cut into segments (few heads, from 8 chunks on), with the
+# last segment shorter, a ragged last chunk, unit counts on and off the
+# XCD-aware order, and one case each side of the cut.  Bar: every chunk rounds
+# the state a few times at 2^-24 of its largest element and later chunks only
+# shrink it, and a segment adds one product with its transition matrix: some tens of
+# 2^-24, 2e-6 (the oracle's fp64 recurrence is the reference).
+@pytest.mark.parametrize("HK,HV,dk,dv,P", [
+    (1, 3, 128, 128, 64 * 9 + 17), (2, 8, 128, 128, 64 * 8), (2, 2, 128, 128, 64 * 7 + 1),
+    (1, 2, 64, 64, 64 * 33 + 5), (1, 1, 32, 32, 64 * 12), (1, 3, 128, 512, 64 * 11 + 63),
+    (2, 2, 256, 256, 64 * 17 + 2), (1, 2, 256, 512, 64 * 9), (4, 8, 128, 256, 64 * 20 + 30)])
+def test_chunked_prefill_segments(HK, HV, dk, dv, P):
+    spec = W.WorkloadSpec(f"pfs_{dk}_{dv}", 1, HK, HV, dk, dv, P, (8,), "bf16", "uniform",
+                          alpha_mu=-5.0, seed=P)
+    wl = W.make_workload(spec)
+    err = state_err(run_chunked(wl), oracle_state(wl))
+    log(f"[prefill] segments dk={dk} dv={dv} P={P} err {err:.2e}")
+    assert err <= 2e-6
