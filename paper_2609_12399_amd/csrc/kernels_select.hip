@@ -13,9 +13,12 @@
 // sort.  Large calls whose workgroups all fit the device at once take the
 // one-pass path (each chunk held in registers from its single read while a
 // bound forms across workgroups, then a placing launch; described at its
-// kernels below); other large calls the two-pass path (wave maxima, then one
-// filter pass, then the one-pass path's placing launch, or ranking
-// workgroups per request beyond 512 chunks); smaller ones a reduction tree.  A 512-thread workgroup holds 16384 candidates (32 per lane):
+// kernels below), those with a few times as many chunks its streaming form
+// (the bound from a sample, the other chunks filtered as they arrive); other
+// large calls the two-pass path (wave maxima, then one filter pass, then the
+// one-pass path's placing launch, or ranking workgroups per request beyond 512
+// chunks); smaller ones a reduction tree.  A 512-thread workgroup holds 16384
+// candidates (32 per lane):
 //   * stage kernel: keeps a superset of its candidates' top min(W, n) and
 //     writes it, in index order, to an output slot of `cap` (key, index)
 //     pairs plus a count.  A 2048-bin histogram of the maxima of groups of
@@ -33,6 +36,7 @@
 // ranges, so position order inside a workgroup is index order, which is what
 // the tie rule needs.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "internal.h"
@@ -57,6 +61,7 @@ constexpr int kRankPer = kThreads / 16;       // survivors ranked per workgroup 
 constexpr int kRankBlocks = kRankCap / kRankPer;
 constexpr int kOnePassRankMax = 1024;         // widest result of the one-pass path
 constexpr int kOnePassFinalParts = 64;       // workgroups per request placing survivors (at most)
+constexpr double kStreamKeep = 1500.0;       // survivors the streaming form may expect
 constexpr int kOnePassSegPer = 8;             // wave summaries per thread of the bound:
                                               // chunks <= kOnePassSegPer * kThreads / 8
 static_assert(kNI == 32, "validity masks are 32-bit");
@@ -86,6 +91,7 @@ struct SelectParams {
   unsigned fparts;          // workgroups per request of the final kernel
   // two-pass path with a bound word per request (see select_summary_kernel)
   unsigned long long* tp_bound;  // [R] (c* + 1) << 32 | B, or null: the filter forms the bound
+  unsigned groups, per;     // streaming form: workgroups per request, chunks per workgroup
 };
 
 // Cross-workgroup state of the one-pass path, at the start of the workspace
@@ -1301,11 +1307,14 @@ __device__ inline unsigned summary_mix(unsigned M, unsigned m, unsigned km) {
 }
 __device__ inline unsigned summary_tag(uint4 e) { return e.w ^ summary_mix(e.x, e.y, e.z); }
 
-// Live lanes of wave w of chunk c (lanes holding at least one candidate).
-__device__ inline unsigned wave_live_lanes(const SelectParams& p, unsigned c, unsigned w) {
+// Live lanes of segment w of chunk c, the chunk's 512 lanes being cut into SPC
+// segments (lanes holding at least one candidate).
+template <int SPC>
+__device__ inline unsigned live_lanes(const SelectParams& p, unsigned c, unsigned w) {
+  constexpr unsigned LANES = unsigned(kThreads / SPC);
   const unsigned nc = min(p.N - c * unsigned(kSelectChunk), unsigned(kSelectChunk));
-  const unsigned first = 64u * w;
-  return nc > first ? min(nc - first, 64u) : 0u;
+  const unsigned first = LANES * w;
+  return nc > first ? min(nc - first, LANES) : 0u;
 }
 
 // LDS of the bound (the request's first workgroup only).
@@ -1323,8 +1332,8 @@ struct BoundShared {
 // the ones beyond nseg outside the buffer, reading zeros); 1 when the waiting
 // time passed first.  No barrier: onepass_bound's first one joins the threads.
 __device__ inline int onepass_poll(const SelectParams& p, unsigned r, unsigned tag,
-                                   uint4 (&e)[kOnePassSegPer]) {
-  const unsigned nseg = p.nseg, t = threadIdx.x;
+                                   uint4 (&e)[kOnePassSegPer], unsigned nseg) {
+  const unsigned t = threadIdx.x;
   const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(p.ex + size_t(r) * nseg, int(nseg * 16u));
   unsigned pending = 0u;
 #pragma unroll
@@ -1362,11 +1371,17 @@ __device__ inline int onepass_poll(const SelectParams& p, unsigned r, unsigned t
 // each other directly.  A bin with more than kBoundList events is split by a
 // second histogram pass over the next 11 bits; should that one hold too many
 // as well, B is its smallest event key (its count still reaches W).
-template <int ROWS = kOnePassSegPer>
+//
+// With SPC = 32 the summaries are those of the 16-lane rows.  chunk_of(i) is the
+// i-th chunk that has summaries, in index order (c* is one of them).
+struct EveryChunk {
+  __device__ unsigned operator()(unsigned i) const { return i; }
+};
+template <int ROWS = kOnePassSegPer, int SPC = kWaves, typename ChunkOf = EveryChunk>
 __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelShared& sh,
                                                    BoundShared& bs, const uint4 (&e)[ROWS],
-                                                   int late, unsigned long long* word) {
-  const unsigned nseg = p.nwg * unsigned(kWaves);
+                                                   int late, unsigned long long* word,
+                                                   unsigned nseg, ChunkOf chunk_of = {}) {
   const unsigned t = threadIdx.x, lane = lane_id(), w = t >> 6;
   const unsigned W = p.W;
   reinterpret_cast<uint4*>(sh.hist)[t] = make_uint4(0u, 0u, 0u, 0u);
@@ -1377,7 +1392,7 @@ __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelSha
     nl[i] = 0u;
     if (unsigned(i) * kThreads < nseg) {
       const unsigned s = unsigned(i) * kThreads + t;
-      nl[i] = s < nseg ? wave_live_lanes(p, s / kWaves, s % kWaves) : 0u;
+      nl[i] = s < nseg ? live_lanes<SPC>(p, chunk_of(s / SPC), s % SPC) : 0u;
       if (nl[i] > 0u) {
         lo = min(lo, e[i].y);
         hi = max(hi, e[i].x);
@@ -1495,21 +1510,25 @@ __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelSha
     __hip_atomic_store(word, (static_cast<unsigned long long>(kCstarPending) << 32) | B,
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // c*: the chunks' guaranteed counts at B, summed in chunk order.  Thread t
-  // holds summary i * kThreads + t, i.e. wave t % 8 of chunk i * 64 + t / 8:
-  // a chunk's count is a sum over 8 adjacent lanes, stored by the first of
-  // them (rows beyond nseg have no live lanes and store zeros); one wave
-  // then scans the chunks in order.
+  // holds summary i * kThreads + t, i.e. segment t % SPC of the chunk numbered
+  // i * kThreads / SPC + t / SPC: a chunk's count is a sum over SPC adjacent
+  // lanes, stored by the first of them (rows beyond nseg have no live lanes
+  // and store zeros); one wave then scans the chunks in order.
+  constexpr unsigned PER = unsigned(kThreads / SPC);
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
     unsigned g = nl[i] > 0u ? (e[i].y >= B ? nl[i] : (e[i].x >= B ? e[i].z : 0u)) : 0u;
     g += dppu<0xB1>(g);   // quad_perm [1,0,3,2]
     g += dppu<0x4E>(g);   // quad_perm [2,3,0,1]
     g += dppu<0x141>(g);  // row_half_mirror: the other quad of the 8 lanes
-    if ((lane & 7u) == 0u) bs.gc[unsigned(i) * 64u + t / 8u] = g;
+    if constexpr (SPC == 32) {
+      g += dppu<0x140>(g);  // row_mirror: the other half of the 16 lanes
+      g += unsigned(__shfl_xor(int(g), 16));
+    }
+    if ((lane & unsigned(SPC - 1)) == 0u) bs.gc[unsigned(i) * PER + t / SPC] = g;
   }
-#pragma unroll
-  for (int i = ROWS; i < kOnePassSegPer; ++i)  // chunks beyond the rows held: none
-    if ((lane & 7u) == 0u) bs.gc[unsigned(i) * 64u + t / 8u] = 0u;
+  if constexpr (unsigned(ROWS) * PER < sizeof(bs.gc) / 4u)  // chunks beyond the rows held: none
+    for (unsigned i = unsigned(ROWS) * PER + t; i < sizeof(bs.gc) / 4u; i += kThreads) bs.gc[i] = 0u;
   if (t == 0) sh.digit = ~0u;  // (c* always exists: the counts at B reach W)
   __syncthreads();
   if (w == 0) {  // lane l: chunks 8 l .. 8 l + 7
@@ -1525,7 +1544,8 @@ __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelSha
     }
   }
   __syncthreads();
-  const unsigned long long bw = (static_cast<unsigned long long>(sh.digit + 1u) << 32) | B;
+  const unsigned long long bw =
+      (static_cast<unsigned long long>(chunk_of(sh.digit) + 1u) << 32) | B;
   if (t == 0) __hip_atomic_store(word, bw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return bw;
 }
@@ -1540,7 +1560,7 @@ struct OnePassShared {
   alignas(16) unsigned long long top[kOnePassRankMax];  // the exact top W
   unsigned bstart[2048];                          // first position of each key bin in buck
   unsigned ntop;
-  unsigned over[kThreads];                        // chunks with more than kSpecEntries survivors
+  unsigned over[kThreads];                        // chunks with more survivors than were loaded with the counts
   unsigned nover;
 };
 
@@ -1717,7 +1737,7 @@ __device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, uns
 // Final stage of request r in one of its nparts workgroups (every chunk's
 // slot and (count, largest key) pair are stored).  One round of loads brings
 // every chunk's count (thread t: chunk t, nchunks <= kThreads) and the first
-// kSpecEntries entries of every slot (coalesced: a wave instruction covers 4
+// entries (kSpecEntries or twice that) of every slot (coalesced: a wave instruction covers 4
 // slots, 16 lanes x 16 bytes each), which holds every survivor of most chunks;
 // the survivors beyond them (a chunk holding many) are loaded by whole
 // waves, one such chunk per wave at a time.  Up to kRankCap survivors are
@@ -1725,8 +1745,12 @@ __device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, uns
 // pass of the exact top-W cut.
 constexpr int kSpecEntries = 32;     // slot entries loaded with the counts
 constexpr int kSpecRows = kThreads / 32;  // 32 slots per row of loads (8 waves x 4 slots)
-constexpr int kBruteRankMax = 2048;  // survivors ranked by direct comparison
-template <bool BEAM>
+// Survivors ranked by direct comparison; through the key histogram beyond (about 1200
+// survivors at 8 requests: 10.5 us compared directly, 7.4 through the histogram).
+constexpr int kBruteRankMax = 1024;
+// With TWO (at most half as many slots as the rows hold) two rows of loads cover each
+// slot, 64 entries: the streaming form leaves more survivors in a chunk.
+template <bool BEAM, bool TWO>
 __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, unsigned r,
                                      unsigned part, unsigned nparts) {
   const unsigned ns = p.nwg, t = threadIdx.x;
@@ -1734,7 +1758,12 @@ __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, un
   SelShared& sh = u.sh;
   const uint2* slots = p.cand_out + size_t(r) * ns * p.cap;
   const unsigned cnt = t < ns ? reinterpret_cast<const uint2*>(p.cnt_out)[size_t(r) * ns + t].x : 0u;
-  uint4 ent[kSpecRows];  // entries 2 (lane % 16), + 1 of slot 32 i + 4 w + lane / 16
+  constexpr int ROWS1 = TWO ? kSpecRows / 2 : kSpecRows;  // rows that cover all slots once
+  constexpr unsigned spec = unsigned(TWO ? 2 * kSpecEntries : kSpecEntries);
+  auto slot_of = [&](int i) { return unsigned(i % ROWS1) * 32u + 4u * w + (lane >> 4); };
+  auto entry_of = [&](int i) { return unsigned(i / ROWS1 * kSpecEntries) + 2u * (lane & 15u); };
+  // entries entry_of(i), + 1 of slot slot_of(i)
+  uint4 ent[kSpecRows];
   // every row is issued (a load under a branch is waited for where the
   // branch joins, which would serialise the rows); rows beyond the request's
   // slots fall outside the buffer and read nothing
@@ -1742,9 +1771,10 @@ __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, un
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(slots, int(ns * p.cap * 8u));
 #pragma unroll
     for (int i = 0; i < kSpecRows; ++i) {
-      const unsigned c = unsigned(i) * 32u + 4u * w + (lane >> 4);
+      // (a slot's capacity is at least 64 entries)
       ent[i] = __builtin_bit_cast(
-          uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (c * p.cap + 2u * (lane & 15u)) * 8u, 0, 0));
+          uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                     rs, (slot_of(i) * p.cap + entry_of(i)) * 8u, 0, 0));
     }
   }
   if (t == 0) u.nover = 0u;
@@ -1762,7 +1792,7 @@ __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, un
   // beyond the request's chunks read as empty
   u.start[t] = t < ns ? start : total;
   if (t == 0) u.start[kThreads] = total;
-  if (cnt > unsigned(kSpecEntries)) u.over[atomicAdd(&u.nover, 1u)] = t;
+  if (cnt > spec) u.over[atomicAdd(&u.nover, 1u)] = t;
   __syncthreads();
   if (total > unsigned(kRankCap)) {  // rare (heavy ties, or a bound that came late)
     // position q lies in the last slot whose start is <= q
@@ -1784,21 +1814,22 @@ __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, un
   unsigned s0[kSpecRows], nn[kSpecRows];
 #pragma unroll
   for (int i = 0; i < kSpecRows; ++i) {  // (no branch around reads: see the loads above)
-    const unsigned c = unsigned(i) * 32u + 4u * w + (lane >> 4);
+    const unsigned c = slot_of(i);
     s0[i] = u.start[c];
     nn[i] = u.start[c + 1] - s0[i];  // 0 beyond the request's chunks
   }
-  const unsigned j = 2u * (lane & 15u), spare = unsigned(kRankCap) + 2u * lane;
+  const unsigned spare = unsigned(kRankCap) + 2u * lane;
 #pragma unroll
   for (int i = 0; i < kSpecRows; ++i)
-    if (unsigned(i) * 32u < ns) {
+    if (unsigned(i % ROWS1) * 32u < ns) {
+      const unsigned j = entry_of(i);
       u.all[j < nn[i] ? s0[i] + j : spare] = composite(make_uint2(ent[i].x, ent[i].y));
       u.all[j + 1u < nn[i] ? s0[i] + j + 1u : spare + 1u] = composite(make_uint2(ent[i].z, ent[i].w));
     }
   for (unsigned i = w; i < u.nover; i += kWaves) {  // wave-uniform
     const unsigned c = u.over[i], s0 = u.start[c], n = u.start[c + 1] - s0;
     const uint2* sl = slots + size_t(c) * p.cap;
-    for (unsigned j0 = kSpecEntries; j0 < n; j0 += 512u) {  // 8 loads per lane in flight
+    for (unsigned j0 = spec; j0 < n; j0 += 512u) {  // 8 loads per lane in flight
       uint2 v[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -1877,8 +1908,8 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
   unsigned long long* const word = &p.ctl->bound[r];
   if (c == 0u) {  // (chunk 0 is never above c*: its bound is B)
     uint4 e[kOnePassSegPer];
-    const int late = onepass_poll(p, r, tag, e);
-    bound = unsigned(onepass_bound(p, sh, bs, e, late, word));
+    const int late = onepass_poll(p, r, tag, e, p.nseg);
+    bound = unsigned(onepass_bound(p, sh, bs, e, late, word, p.nseg));
   } else {
     if (t == 0) bw_sh[0] = wait_bound(word, p.wait_ticks, false);
     __syncthreads();
@@ -1925,6 +1956,234 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
   }
 }
 
+// Streaming form, for calls with more chunks than workgroups fit the device:
+// p.groups workgroups per request (all resident, as above) take p.per consecutive
+// chunks each.  The chunk that a workgroup reads first, one in p.per of the request's,
+// serves as a sample (the first chunk of one workgroup, the last of the next, the
+// request's first and last among them, so that scores that fall or rise with the
+// beam show their best): its summaries form the bound (which holds for all candidates, since W of
+// the sample's reach it), while the next two chunks arrive, and these are filtered
+// as soon as it is there.  So every score is read once, and about p.per
+// times as many candidates survive as with a bound from all chunks.  Summaries
+// are taken per 16-lane row (SPC = 32) where they fit, because the sample has fewer
+// waves and the guaranteed counts need about three times W of them to be tight.
+//   Bound: the first chunk's round trip and the bound (about 12 us), then per
+// chunk a barrier-separated compaction by one workgroup per compute unit (8 x 256 x
+// 8192, 67 MB in four chunks per workgroup: 31.6 us; a plain read takes 10.5).  With
+// keys in place of scores 34.5 us; three chunks ahead in place of two 38 us (the
+// polls of the bound wait behind the loads: the vector memory counter retires in
+// order).
+
+// The log-probabilities of a chunk on their way: the beam scores are added when they
+// have come.
+struct RawScores {
+  float x[kNI];
+  unsigned vm;
+};
+template <bool BEAM>
+__device__ inline void issue_scores(const SelectParams& p, unsigned r, unsigned base, unsigned n,
+                                    RawScores& l) {
+  l.vm = valid_mask(n);
+  const float* logp_r = p.logp + size_t(r) * p.N;
+#pragma unroll
+  for (int i = 0; i < kNI; ++i)
+    l.x[i] = logp_r[((l.vm >> i) & 1u) ? base + threadIdx.x + unsigned(i) * kThreads : base];
+}
+
+// Candidate scores of the loaded chunk; invalid slots are NaN, which no bound keeps.
+// Where each wave's slot lies in one row and a chunk in at most 34 rows, the beam
+// scores are one load (lane l: row row0 + l) and a lane read per slot; otherwise a
+// load per slot.  The streaming form works on scores and forms keys only for
+// the lanes' maxima and the survivors: at four chunks per compute unit the keys' ten
+// vector instructions per candidate cost more than the reads (a plain read of 67 MB
+// takes 10.5 us here).
+template <bool BEAM>
+__device__ inline void score_vals(const SelectParams& p, unsigned r, unsigned base,
+                                  const RawScores& l, float (&v)[kNI]) {
+  const float nan = __uint_as_float(0x7fc00000u);
+  if constexpr (!BEAM) {
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) v[i] = l.x[i];
+  } else {
+    const float* beam_r = p.beam + size_t(r) * p.W_prev;
+    if (p.V >= unsigned(kThreads) && (p.V & 63u) == 0u) {
+      const unsigned row0 = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(base, p.V, p.inv_v))));
+      const float bv = beam_r[min(row0 + lane_id(), p.W_prev - 1u)];
+      unsigned rel = 0u;  // of the wave's slot: its row, from row0, and its offset there
+      unsigned rem = base + unsigned(__builtin_amdgcn_readfirstlane(int(threadIdx.x & ~63u))) - row0 * p.V;
+      if (rem >= p.V) {
+        rem -= p.V;
+        ++rel;
+      }
+#pragma unroll
+      for (int i = 0; i < kNI; ++i) {
+        v[i] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bv), rel)) + l.x[i];
+        rem += kThreads;
+        if (rem >= p.V) {
+          rem -= p.V;
+          ++rel;
+        }
+      }
+    } else {
+      float bs[kNI];
+#pragma unroll
+      for (int i = 0; i < kNI; ++i) {
+        const unsigned pos = base + threadIdx.x + unsigned(i) * kThreads;
+        bs[i] = beam_r[((l.vm >> i) & 1u) ? row_of(pos, p.V, p.inv_v) : 0u];
+      }
+#pragma unroll
+      for (int i = 0; i < kNI; ++i) v[i] = bs[i] + l.x[i];
+    }
+  }
+  if (__ballot(l.vm != ~0u) != 0ull) {  // (a whole chunk has no invalid slot)
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) v[i] = ((l.vm >> i) & 1u) ? v[i] : nan;
+  }
+}
+
+template <bool BEAM, int SPC>
+__global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p) {
+  __shared__ SelShared sh;
+  __shared__ BoundShared bs;
+  __shared__ unsigned long long bw_sh[1];
+  const unsigned r = blockIdx.x / p.groups, g = blockIdx.x - r * p.groups;
+  const unsigned t = threadIdx.x, lane = lane_id(), w = t >> 6;
+  const unsigned tag = p.ctl->epoch + 1u;  // (the final kernel advances the epoch)
+  // chunks c0 .. c0 + nc - 1 (at least one), read from the last on where `back`
+  auto backwards = [&](unsigned i) { return (i & 1u) != 0u || (i != 0u && i == p.groups - 1u); };
+  auto sampled = [&](unsigned i) {
+    return backwards(i) ? min((i + 1u) * p.per, p.nwg) - 1u : i * p.per;
+  };
+  const unsigned c0 = g * p.per, nc = min(p.per, p.nwg - c0), first = sampled(g);
+  const bool back = backwards(g);
+  const unsigned nseg = p.groups * unsigned(SPC);
+  auto chunk_at = [&](unsigned j) __attribute__((always_inline)) {  // the j-th read (clamped)
+    const unsigned i = min(j, nc - 1u);
+    return back ? first - i : first + i;
+  };
+  auto base_of = [&](unsigned j) __attribute__((always_inline)) {
+    return chunk_at(j) * unsigned(kSelectChunk);
+  };
+  auto issue = [&](unsigned j, RawScores& l) __attribute__((always_inline)) {  // (past the last: none valid)
+    const unsigned base = base_of(j);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_scores<BEAM>(p, r, base, j < nc ? min(p.N - base, unsigned(kSelectChunk)) : 0u, l);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  float val[kNI], val1[kNI];  // the chunks read as 0, 2, ... and as 1, 3, ...
+  RawScores la, lb;
+  issue(0u, la);
+  score_vals<BEAM>(p, r, base_of(0u), la, val);
+  const unsigned vm = la.vm;
+  issue(1u, lb);
+  {  // the first chunk's summaries (the largest of a lane's numbers; key 0 if it has none)
+    float best = val[0];
+#pragma unroll
+    for (int i = 1; i < kNI; ++i) best = fmaxf(best, val[i]);
+    const unsigned lmax = order_key(best);
+    const bool live = vm & 1u;
+    if constexpr (SPC == kWaves) {
+      const Red3 wr = wave_reduce(0u, live ? lmax : ~0u, lmax);
+      const unsigned km = unsigned(__popcll(__ballot(live && lmax == wr.hi)));
+      if (lane == 0)
+        st_agent4(p.ex, (r * nseg + g * SPC + w) * 16u,
+                  make_uint4(wr.hi, wr.lo, km, tag ^ summary_mix(wr.hi, wr.lo, km)));
+    } else {
+      unsigned hi = lmax, lo = live ? lmax : ~0u;
+      hi = max(hi, dppu<0xB1>(hi));
+      lo = min(lo, dppu<0xB1>(lo));
+      hi = max(hi, dppu<0x4E>(hi));
+      lo = min(lo, dppu<0x4E>(lo));
+      hi = max(hi, dppu<0x141>(hi));
+      lo = min(lo, dppu<0x141>(lo));
+      hi = max(hi, dppu<0x140>(hi));
+      lo = min(lo, dppu<0x140>(lo));
+      const unsigned long long at = __ballot(live && lmax == hi);
+      const unsigned km = unsigned(__popc(unsigned(at >> (lane & 48u)) & 0xffffu));
+      if ((lane & 15u) == 0u)
+        st_agent4(p.ex, (r * nseg + g * SPC + t / 16u) * 16u,
+                  make_uint4(hi, lo, km, tag ^ summary_mix(hi, lo, km)));
+    }
+  }
+  unsigned long long* const word = &p.ctl->bound[r];
+  unsigned long long bw;
+  if (g == 0u) {
+    uint4 e[kOnePassSegPer];
+    const int late = onepass_poll(p, r, tag, e, nseg);
+    bw = onepass_bound<kOnePassSegPer, SPC>(p, sh, bs, e, late, word, nseg, sampled);
+    score_vals<BEAM>(p, r, base_of(1u), lb, val1);
+    issue(2u, la);
+  } else {
+    // (the second chunk's scores are formed while the bound is, and the third's
+    // loads issued; B and c*: c* comes about 1 us after B, and chunks after the
+    // first need it)
+    score_vals<BEAM>(p, r, base_of(1u), lb, val1);
+    issue(2u, la);
+    if (t == 0) bw_sh[0] = wait_bound(word, p.wait_ticks, true);
+    __syncthreads();
+    bw = bw_sh[0];  // 0 after a timeout: no bound
+  }
+  const unsigned B = unsigned(bw), cstar = unsigned(bw >> 32) - 1u;
+  auto bound_of = [&](unsigned c) { return (c > cstar && B < ~0u) ? B + 1u : B; };
+  unsigned long long over = 0ull;  // reads whose survivors overflow their slot
+  // (inlined by force: called, the lambdas' captures, the keys among them, would
+  // live in scratch)
+  auto filter = [&](unsigned j, unsigned vmask, const float(&v)[kNI]) __attribute__((always_inline)) {
+    const unsigned c = chunk_at(j), bound = bound_of(c), base = c * unsigned(kSelectChunk);
+    // the bound as a score: every number whose key reaches it compares at or above
+    // it (and the other zero with it, which the placing orders); 1 .. the key of
+    // -inf keep every number, 0 everything
+    const float bf = bound <= 0x007fffffu ? -INFINITY
+                                          : __uint_as_float(bound & 0x80000000u ? bound ^ 0x80000000u : ~bound);
+    unsigned keep = 0u;
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) keep |= v[i] >= bf ? 1u << i : 0u;
+    keep = bound == 0u ? vmask : keep;
+    const unsigned total = replan_sparse(keep, sh);
+    if (total > p.cap) {  // rare: cut below, from a second read
+      over |= 1ull << j;
+    } else {
+      uint2* out = p.cand_out + (size_t(r) * p.nwg + c) * p.cap;
+      ordered_apply_sparse(keep, sh, [&](int i, unsigned rank) __attribute__((always_inline)) {
+        out[rank] = make_uint2(order_key(v[i]), base + unsigned(i) * kThreads + t);
+      });
+      if (t == 0)  // (the placing kernel does not read a largest key)
+        reinterpret_cast<uint2*>(p.cnt_out)[size_t(r) * p.nwg + c] = make_uint2(total, 0u);
+    }
+    __syncthreads();  // every wave has read sh.tab
+  };
+  filter(0u, vm, val);
+  for (unsigned j = 1u; j < nc; j += 2u) {
+    const unsigned vm1 = lb.vm;
+    issue(j + 2u, lb);
+    filter(j, vm1, val1);
+    if (j + 1u == nc) break;
+    score_vals<BEAM>(p, r, base_of(j + 1u), la, val);
+    const unsigned vm0 = la.vm;
+    issue(j + 3u, la);
+    filter(j + 1u, vm0, val);
+    if (j + 2u < nc) score_vals<BEAM>(p, r, base_of(j + 2u), lb, val1);
+  }
+  for (; over != 0ull; over &= over - 1ull) {  // a chunk's exact top W of its survivors
+    const unsigned c = chunk_at(unsigned(__builtin_ctzll(over))), bound = bound_of(c);
+    const unsigned base = c * unsigned(kSelectChunk);
+    unsigned key[kNI];
+    unsigned keep = load_raw<BEAM>(p, r, base, min(p.N - base, unsigned(kSelectChunk)), key);
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) keep &= ~(unsigned(key[i] < bound) << i);
+    __syncthreads();
+    keep = cut_mask(sh, key, keep, find_cut(sh, key, keep, p.W));
+    const unsigned total = replan_sparse(keep, sh);
+    uint2* out = p.cand_out + (size_t(r) * p.nwg + c) * p.cap;
+    ordered_apply_sparse(keep, sh, [&](int i, unsigned rank) __attribute__((always_inline)) {
+      out[rank] = make_uint2(key[i], base + unsigned(i) * kThreads + t);
+    });
+    if (t == 0)
+      reinterpret_cast<uint2*>(p.cnt_out)[size_t(r) * p.nwg + c] = make_uint2(total, 0u);
+    __syncthreads();
+  }
+}
+
 // Advances the epoch past this call's tag (workgroup 0 of the final kernel).
 // After the largest tag it starts again at 0, and the summary region is
 // cleared first, so that no summary left there carries a later call's tag.
@@ -1943,7 +2202,7 @@ __device__ inline void advance_epoch(const SelectParams& p) {
 // request's bound word to zero for the next call, and workgroup 0 advances
 // the epoch.  (Without a control block, as after the two-pass filter, it
 // only places.)
-template <bool BEAM>
+template <bool BEAM, bool TWO>
 __global__ __launch_bounds__(kThreads) void select_onepass_final_kernel(SelectParams p) {
   __shared__ OnePassShared u;
   const unsigned r = blockIdx.x / p.fparts;
@@ -1952,7 +2211,7 @@ __global__ __launch_bounds__(kThreads) void select_onepass_final_kernel(SelectPa
     if (threadIdx.x == 0 && part == 0u) p.ctl->bound[r] = 0ull;
     if (blockIdx.x == 0u) advance_epoch(p);
   }
-  onepass_final<BEAM>(p, u, r, part, p.fparts);
+  onepass_final<BEAM, TWO>(p, u, r, part, p.fparts);
 }
 
 
@@ -1991,7 +2250,7 @@ __global__ __launch_bounds__(kThreads) void select_summary_kernel(SelectParams p
   const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(p.ex + size_t(r) * p.nseg, int(p.nseg * 16u));
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) e[i] = ld_agent4(rs, (unsigned(i) * kThreads + t) * 16u);
-  onepass_bound<ROWS>(p, sh, bs, e, 0, &p.tp_bound[r]);
+  onepass_bound<ROWS>(p, sh, bs, e, 0, &p.tp_bound[r], p.nseg);
   if (t == 0) p.ctl->arrive[r] = 0u;
 }
 
@@ -2000,7 +2259,7 @@ __global__ __launch_bounds__(kThreads) void select_summary_kernel(SelectParams p
 // ones that cannot start), and its wait for the bound in wall-clock ticks;
 // both queried once per device.
 struct OnePassDevice {
-  unsigned capacity;
+  unsigned capacity, stream_capacity;
   unsigned long long wait_ticks;
 };
 OnePassDevice onepass_device() {
@@ -2009,10 +2268,10 @@ OnePassDevice onepass_device() {
   static OnePassDevice cache[kMaxDevices] = {};
   static bool known[kMaxDevices] = {};
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return {0u, 0ull};
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return {0u, 0u, 0ull};
   std::lock_guard<std::mutex> lock(mu);
   if (!known[dev]) {
-    OnePassDevice d{0u, 0ull};
+    OnePassDevice d{0u, 0u, 0ull};
     int cus = 0, per_cu_a = 0, per_cu_b = 0, khz = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
         hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -2025,6 +2284,17 @@ OnePassDevice onepass_device() {
         cus > 0 && khz > 0) {
       d.capacity = unsigned(cus) * unsigned(std::min(per_cu_a, per_cu_b));
       d.wait_ticks = 20ull * unsigned(khz) / 1000ull;  // 20 us
+      const void* stream[4] = {reinterpret_cast<const void*>(select_stream_kernel<true, kWaves>),
+                               reinterpret_cast<const void*>(select_stream_kernel<false, kWaves>),
+                               reinterpret_cast<const void*>(select_stream_kernel<true, 32>),
+                               reinterpret_cast<const void*>(select_stream_kernel<false, 32>)};
+      int least = per_cu_a;
+      for (const void* f : stream) {
+        int per = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, kThreads, 0) != hipSuccess) per = 0;
+        least = std::min(least, per);
+      }
+      d.stream_capacity = unsigned(cus) * unsigned(least);
     }
     cache[dev] = d;
     known[dev] = true;
@@ -2032,6 +2302,30 @@ OnePassDevice onepass_device() {
   return cache[dev];
 }
 unsigned onepass_capacity() { return onepass_device().capacity; }
+
+// Workgroups per request of the streaming form, and the segments of a chunk
+// that have summaries; 0 when the call is not for it.  Measured against the two
+// passes (wave maxima or summaries, then the filter; us per launch, with the placing
+// launch): 8 requests x 256 x 8192 -> 256 31.6 + 6.5 against 22.3 + 22.3 + 4.8; 4 x 256 x
+// 8192 20.8 + 4.6 against 9.1 + 19.2 + 4.0; 2 x 512 x 8192 -> 512 20.8 + 6.7 against
+// 9.0 + 19.6 + 4.6.  With more expected survivors than kStreamKeep the placing
+// takes longer than the pass saves: 1024 x 8192 -> 1024 (2800 expected) 21.8 + 55.6
+// against 9.0 + 21.0 + 7.1; 16 x 256 x 8192 -> 256 (2840) 66 + 37 against 38 + 43 + 6.
+struct StreamPlan {
+  unsigned groups, per, spc;
+};
+StreamPlan stream_plan(unsigned R, unsigned nchunks, unsigned W) {
+  const unsigned most = onepass_device().stream_capacity / R;
+  if (most == 0u) return {0u, 0u, 0u};
+  const unsigned per = (nchunks + most - 1u) / most, groups = (nchunks + per - 1u) / per;
+  const unsigned spc = groups * 32u <= unsigned(kOnePassSegPer * kThreads) ? 32u : unsigned(kWaves);
+  // Candidates of the sample above the bound: W of the nseg segments reach it, so
+  // a segment holds on average -ln(1 - W / nseg) of them.
+  const double nseg = double(groups) * spc;
+  if (double(W) > 0.9 * nseg || per > 64u) return {0u, 0u, 0u};
+  if (-nseg * std::log1p(-double(W) / nseg) * per > kStreamKeep) return {0u, 0u, 0u};
+  return {groups, per, spc};
+}
 unsigned long long onepass_wait_ticks() { return onepass_device().wait_ticks; }
 
 }  // namespace
@@ -2075,9 +2369,43 @@ hipError_t launch_select(const SelectPlan& plan, int R, int prev_width, int voca
     // workgroups (one per compute unit)
     p.fparts = std::max(1u, std::min(unsigned(kOnePassFinalParts), 256u / unsigned(R)));
     const unsigned fblocks = unsigned(R) * p.fparts;
-    if (has_beam) select_onepass_final_kernel<true><<<fblocks, kThreads, 0, st>>>(p);
-    else select_onepass_final_kernel<false><<<fblocks, kThreads, 0, st>>>(p);
+    if (has_beam) select_onepass_final_kernel<true, false><<<fblocks, kThreads, 0, st>>>(p);
+    else select_onepass_final_kernel<false, false><<<fblocks, kThreads, 0, st>>>(p);
     return hipGetLastError();
+  }
+  if (plan.two_pass && R <= kSelectOnePassMaxRequests && width <= kOnePassRankMax &&
+      plan.nchunks <= unsigned(kThreads)) {
+    const StreamPlan sp = stream_plan(unsigned(R), plan.nchunks, p.W);
+    if (sp.groups > 0u && size_t(R) * sp.groups * sp.spc * 16u <= kSelectSummaryBytes) {
+      p.ctl = reinterpret_cast<OnePassCtl*>(ws);
+      p.ex = reinterpret_cast<uint4*>(ws + kSelectCtlBytes);
+      p.nwg = plan.nchunks;
+      p.groups = sp.groups;
+      p.per = sp.per;
+      p.cand_out = reinterpret_cast<uint2*>(ws + plan.slot_off);
+      p.cnt_out = reinterpret_cast<unsigned*>(ws + plan.cnt_off);
+      p.wait_ticks = onepass_wait_ticks();
+      const unsigned blocks = unsigned(R) * sp.groups;
+      if (sp.spc == 32u) {
+        if (has_beam) select_stream_kernel<true, 32><<<blocks, kThreads, 0, st>>>(p);
+        else select_stream_kernel<false, 32><<<blocks, kThreads, 0, st>>>(p);
+      } else {
+        if (has_beam) select_stream_kernel<true, kWaves><<<blocks, kThreads, 0, st>>>(p);
+        else select_stream_kernel<false, kWaves><<<blocks, kThreads, 0, st>>>(p);
+      }
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      p.fparts = std::max(1u, std::min(unsigned(kOnePassFinalParts), 256u / unsigned(R)));
+      const unsigned fblocks = unsigned(R) * p.fparts;
+      if (p.nwg <= unsigned(kThreads / 2)) {
+        if (has_beam) select_onepass_final_kernel<true, true><<<fblocks, kThreads, 0, st>>>(p);
+        else select_onepass_final_kernel<false, true><<<fblocks, kThreads, 0, st>>>(p);
+      } else {
+        if (has_beam) select_onepass_final_kernel<true, false><<<fblocks, kThreads, 0, st>>>(p);
+        else select_onepass_final_kernel<false, false><<<fblocks, kThreads, 0, st>>>(p);
+      }
+      return hipGetLastError();
+    }
   }
   if (plan.two_pass) {
     p.nseg = plan.nseg;
@@ -2129,8 +2457,8 @@ hipError_t launch_select(const SelectPlan& plan, int R, int prev_width, int voca
       p.ctl = nullptr;
       p.fparts = std::max(1u, std::min(unsigned(kOnePassFinalParts), 256u / unsigned(R)));
       const unsigned fblocks = unsigned(R) * p.fparts;
-      if (has_beam) select_onepass_final_kernel<true><<<fblocks, kThreads, 0, st>>>(p);
-      else select_onepass_final_kernel<false><<<fblocks, kThreads, 0, st>>>(p);
+      if (has_beam) select_onepass_final_kernel<true, false><<<fblocks, kThreads, 0, st>>>(p);
+      else select_onepass_final_kernel<false, false><<<fblocks, kThreads, 0, st>>>(p);
       return hipGetLastError();
     }
     p.cand_in = p.cand_out;

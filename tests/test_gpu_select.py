@@ -59,6 +59,18 @@ CASES = [
     ("two_pass_summary_rising_r8", 8, 256, SELECT_CODEBOOK, 256, "rising", True),
     ("two_pass_summary_r4_w1024_ties", 4, 1024, 4096, 1024, "ties", True),
     ("two_pass_summary_rows8", 2, 1024, SELECT_CODEBOOK, 256, "logsoftmax", True),
+    # streaming form (more chunks than fit at once; two to four per workgroup):
+    # rows that straddle a wave's slot and a ragged last chunk with special
+    # values, rows shorter than a workgroup, no beam scores, a row per 16
+    # lanes' and per wave's summaries, slots that overflow, W = 1, one
+    # workgroup with fewer chunks than the others
+    ("stream_special_ragged", 3, 500, 3001, 200, "special", True),
+    ("stream_short_rows", 3, 5000, 300, 128, "logsoftmax", True),
+    ("stream_no_beam", 5, 108, SELECT_CODEBOOK, 150, "special", False),
+    ("stream_wave_summaries", 1, 530, SELECT_CODEBOOK, 200, "logsoftmax", True),
+    ("stream_rising_overflow", 4, 133, SELECT_CODEBOOK, 40, "rising", True),
+    ("stream_ties_overflow", 4, 131, SELECT_CODEBOOK, 33, "ties", True),
+    ("stream_width_one", 9, 60, SELECT_CODEBOOK, 1, "logsoftmax", True),
 ]
 
 
