@@ -224,6 +224,24 @@ __device__ inline unsigned order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// A bound key as a score: every number whose key reaches the bound compares at or
+// above it (and so does the other zero with it, which the placing orders); a
+// bound of 1 up to the key of -inf keeps every number.  A bound of 0 keeps
+// everything, NaNs too, and is for the caller to see.
+__device__ inline float bound_score(unsigned key) {
+  if (key <= 0x007fffffu) return -INFINITY;
+  return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
+}
+
+// Slots of v that a bound keeps, among the valid ones.
+__device__ inline unsigned kept_mask(const float (&v)[kNI], unsigned vm, unsigned bound) {
+  const float b = bound_score(bound);
+  unsigned keep = 0u;
+#pragma unroll
+  for (int i = 0; i < kNI; ++i) keep |= v[i] >= b ? 1u << i : 0u;
+  return bound == 0u ? vm : keep;
+}
+
 // Row (beam) of a flat index: the fp64 quotient is within 1/V of the true
 // one, so one correction step makes it exact.
 __device__ inline unsigned row_of(unsigned idx, unsigned V, double inv_v) {
@@ -495,13 +513,13 @@ __device__ inline unsigned valid_mask(unsigned n) {
   return nv >= 32u ? ~0u : (1u << nv) - 1u;
 }
 
-// Raw scores at chunk positions [base, base + n) of request r.  Invalid slots
-// get key 0.  Every lane issues all of its loads before using any (invalid
+// Candidate scores at chunk positions [base, base + n) of request r; invalid slots are
+// NaN (the order's last: key 0).  Every lane issues all of its loads before using any (invalid
 // slots read a clamped, in-bounds address), so the chunk streams in one
 // round trip.
 template <bool BEAM>
-__device__ inline unsigned load_raw(const SelectParams& p, unsigned r, unsigned base, unsigned n,
-                                    unsigned (&key)[kNI]) {
+__device__ inline unsigned load_scores(const SelectParams& p, unsigned r, unsigned base, unsigned n,
+                                    float (&v)[kNI]) {
   const unsigned vm = valid_mask(n);
   const float* logp_r = p.logp + size_t(r) * p.N;
   const float* beam_r = BEAM ? p.beam + size_t(r) * p.W_prev : nullptr;
@@ -536,10 +554,21 @@ __device__ inline unsigned load_raw(const SelectParams& p, unsigned r, unsigned 
   }
 #pragma unroll
   for (int i = 0; i < kNI; ++i) {
-    float v = x[i];
-    if constexpr (BEAM) v = bs[i] + v;
-    key[i] = ((vm >> i) & 1u) ? order_key(v) : 0u;
+    v[i] = x[i];
+    if constexpr (BEAM) v[i] = bs[i] + v[i];
+    v[i] = ((vm >> i) & 1u) ? v[i] : __uint_as_float(0x7fc00000u);
   }
+  return vm;
+}
+
+// Their keys; invalid slots get key 0.
+template <bool BEAM>
+__device__ inline unsigned load_raw(const SelectParams& p, unsigned r, unsigned base, unsigned n,
+                                    unsigned (&key)[kNI]) {
+  float v[kNI];
+  const unsigned vm = load_scores<BEAM>(p, r, base, n, v);
+#pragma unroll
+  for (int i = 0; i < kNI; ++i) key[i] = order_key(v[i]);
   return vm;
 }
 
@@ -1888,13 +1917,14 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
   const unsigned n = min(p.N - base, unsigned(kSelectChunk));
   const unsigned t = threadIdx.x, w = t >> 6;
   const unsigned tag = p.ctl->epoch + 1u;  // (the final kernel advances the epoch)
-  unsigned key[kNI];
-  const unsigned vm = load_raw<BEAM>(p, r, base, n, key);
+  float v[kNI];  // (keys only of the lanes' maxima and of the survivors)
+  const unsigned vm = load_scores<BEAM>(p, r, base, n, v);
   if (t < (kNI * kWaves + 4) / 4) reinterpret_cast<uint4*>(sh.tab)[t] = make_uint4(0u, 0u, 0u, 0u);
   // 1. this wave's (M, m), published with the call's tag
-  unsigned lmax = 0u;  // invalid slots hold key 0
+  float best = v[0];
 #pragma unroll
-  for (int i = 0; i < kNI; ++i) lmax = max(lmax, key[i]);
+  for (int i = 1; i < kNI; ++i) best = fmaxf(best, v[i]);
+  const unsigned lmax = order_key(best);
   const Red3 wr = wave_reduce(0u, (vm & 1u) ? lmax : ~0u, lmax);
   const unsigned km = unsigned(__popcll(__ballot((vm & 1u) && lmax == wr.hi)));
   if (lane_id() == 0) {
@@ -1917,10 +1947,13 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
     if (unsigned(bw >> 32) == kCstarPending) {
       // c* decides only for keys equal to B: a chunk holding none keeps the
       // keys >= B whichever side of c* it is on
+      // (compared as scores: the other zero counts as equal, and so does anything
+      // where B is not the key of a finite score)
       const unsigned B = unsigned(bw);
-      int eq = 0;
+      const float b = bound_score(B);
+      int eq = int(B <= 0x007fffffu);
 #pragma unroll
-      for (int i = 0; i < kNI; ++i) eq |= int(((vm >> i) & 1u) && key[i] == B);
+      for (int i = 0; i < kNI; ++i) eq |= int(v[i] == b);
       if (__syncthreads_or(eq)) {
         if (t == 0) bw_sh[0] = wait_bound(word, p.wait_ticks, true);
         __syncthreads();
@@ -1932,15 +1965,16 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
   }
   // 3. survivors into the chunk's slot (as the filter kernel); the final
   // kernel reads them after this launch has ended
-  unsigned keep = vm;
-#pragma unroll
-  for (int i = 0; i < kNI; ++i) keep &= ~(unsigned(key[i] < bound) << i);
+  unsigned keep = kept_mask(v, vm, bound);
   uint2* out = p.cand_out + (size_t(r) * p.nwg + c) * p.cap;
   auto put = [&](int i, unsigned rank) {
-    out[rank] = make_uint2(key[i], base + unsigned(i) * kThreads + t);
+    out[rank] = make_uint2(order_key(v[i]), base + unsigned(i) * kThreads + t);
   };
   unsigned total = ordered_plan_sparse(keep, sh);
   if (total > p.cap) {  // a chunk's exact top W of its survivors
+    unsigned key[kNI];
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) key[i] = order_key(v[i]);
     __syncthreads();
     keep = cut_mask(sh, key, keep, find_cut(sh, key, keep, p.W));
     total = replan_sparse(keep, sh);
@@ -2130,15 +2164,7 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p)
   // live in scratch)
   auto filter = [&](unsigned j, unsigned vmask, const float(&v)[kNI]) __attribute__((always_inline)) {
     const unsigned c = chunk_at(j), bound = bound_of(c), base = c * unsigned(kSelectChunk);
-    // the bound as a score: every number whose key reaches it compares at or above
-    // it (and the other zero with it, which the placing orders); 1 .. the key of
-    // -inf keep every number, 0 everything
-    const float bf = bound <= 0x007fffffu ? -INFINITY
-                                          : __uint_as_float(bound & 0x80000000u ? bound ^ 0x80000000u : ~bound);
-    unsigned keep = 0u;
-#pragma unroll
-    for (int i = 0; i < kNI; ++i) keep |= v[i] >= bf ? 1u << i : 0u;
-    keep = bound == 0u ? vmask : keep;
+    const unsigned keep = kept_mask(v, vmask, bound);
     const unsigned total = replan_sparse(keep, sh);
     if (total > p.cap) {  // rare: cut below, from a second read
       over |= 1ull << j;
