@@ -233,6 +233,14 @@ __device__ inline float bound_score(unsigned key) {
   return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
 
+// The largest number of a lane (NaN if it has none: key 0).
+__device__ inline float lane_best(const float (&v)[kNI]) {
+  float best = v[0];
+#pragma unroll
+  for (int i = 1; i < kNI; ++i) best = fmaxf(best, v[i]);
+  return best;
+}
+
 // Slots of v that a bound keeps, among the valid ones.
 __device__ inline unsigned kept_mask(const float (&v)[kNI], unsigned vm, unsigned bound) {
   const float b = bound_score(bound);
@@ -875,12 +883,9 @@ __global__ __launch_bounds__(kThreads) void select_segmax_kernel(SelectParams p)
   const unsigned r = blockIdx.x / p.nwg, c = blockIdx.x - r * p.nwg;
   const unsigned base = c * unsigned(kSelectChunk);
   const unsigned n = min(p.N - base, unsigned(kSelectChunk));
-  unsigned key[kNI];
-  load_raw<BEAM>(p, r, base, n, key);
-  unsigned mx = 0u;
-#pragma unroll
-  for (int i = 0; i < kNI; ++i) mx = max(mx, key[i]);  // invalid slots hold 0
-  const Red3 w = wave_reduce(0u, 0u, mx);
+  float v[kNI];
+  load_scores<BEAM>(p, r, base, n, v);
+  const Red3 w = wave_reduce(0u, 0u, order_key(lane_best(v)));
   if (lane_id() == 0) p.segmax[size_t(r) * p.nseg + c * kWaves + (threadIdx.x >> 6)] = w.hi;
 }
 
@@ -890,8 +895,8 @@ __global__ __launch_bounds__(kThreads) void select_filter_kernel(SelectParams p)
   const unsigned r = blockIdx.x / p.nwg, c = blockIdx.x - r * p.nwg;
   const unsigned base = c * unsigned(kSelectChunk);
   const unsigned n = min(p.N - base, unsigned(kSelectChunk));
-  unsigned key[kNI];
-  const unsigned vm = load_raw<BEAM>(p, r, base, n, key);
+  float v[kNI];
+  const unsigned vm = load_scores<BEAM>(p, r, base, n, v);
   unsigned bound;
   if constexpr (WORD) {
     // the request's bound word, formed in the summary pass as the one-pass
@@ -923,18 +928,19 @@ __global__ __launch_bounds__(kThreads) void select_filter_kernel(SelectParams p)
     // their count from the top reaches W)
     bound = group_bound(sh, mk, mvm, p.W, 1u);
   }
-  unsigned keep = vm;
-#pragma unroll
-  for (int i = 0; i < kNI; ++i) keep &= ~(unsigned(key[i] < bound) << i);
+  unsigned keep = kept_mask(v, vm, bound);
   if (threadIdx.x < (kNI * kWaves + 4) / 4)  // the sparse compaction's zero counts
     reinterpret_cast<uint4*>(sh.tab)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
   uint2* out = p.cand_out + (size_t(r) * p.nwg + c) * p.cap;
   auto put = [&](int i, unsigned rank) {
-    out[rank] = make_uint2(key[i], base + unsigned(i) * kThreads + threadIdx.x);
+    out[rank] = make_uint2(order_key(v[i]), base + unsigned(i) * kThreads + threadIdx.x);
   };
   unsigned total = ordered_plan_sparse(keep, sh);
   if (total > p.cap) {  // rare: keep the chunk's exact top W of the survivors
+    unsigned key[kNI];
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) key[i] = order_key(v[i]);
     __syncthreads();
     keep = cut_mask(sh, key, keep, find_cut(sh, key, keep, p.W));
     total = replan_sparse(keep, sh);
@@ -1921,10 +1927,7 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
   const unsigned vm = load_scores<BEAM>(p, r, base, n, v);
   if (t < (kNI * kWaves + 4) / 4) reinterpret_cast<uint4*>(sh.tab)[t] = make_uint4(0u, 0u, 0u, 0u);
   // 1. this wave's (M, m), published with the call's tag
-  float best = v[0];
-#pragma unroll
-  for (int i = 1; i < kNI; ++i) best = fmaxf(best, v[i]);
-  const unsigned lmax = order_key(best);
+  const unsigned lmax = order_key(lane_best(v));
   const Red3 wr = wave_reduce(0u, (vm & 1u) ? lmax : ~0u, lmax);
   const unsigned km = unsigned(__popcll(__ballot((vm & 1u) && lmax == wr.hi)));
   if (lane_id() == 0) {
@@ -2111,10 +2114,7 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p)
   const unsigned vm = la.vm;
   issue(1u, lb);
   {  // the first chunk's summaries (the largest of a lane's numbers; key 0 if it has none)
-    float best = val[0];
-#pragma unroll
-    for (int i = 1; i < kNI; ++i) best = fmaxf(best, val[i]);
-    const unsigned lmax = order_key(best);
+    const unsigned lmax = order_key(lane_best(val));
     const bool live = vm & 1u;
     if constexpr (SPC == kWaves) {
       const Red3 wr = wave_reduce(0u, live ? lmax : ~0u, lmax);
@@ -2258,11 +2258,9 @@ __global__ __launch_bounds__(kThreads) void select_summary_kernel(SelectParams p
   const unsigned base = c * unsigned(kSelectChunk);
   const unsigned n = min(p.N - base, unsigned(kSelectChunk));
   const unsigned t = threadIdx.x, w = t >> 6;
-  unsigned key[kNI];
-  const unsigned vm = load_raw<BEAM>(p, r, base, n, key);
-  unsigned lmax = 0u;  // invalid slots hold key 0
-#pragma unroll
-  for (int i = 0; i < kNI; ++i) lmax = max(lmax, key[i]);
+  float v[kNI];
+  const unsigned vm = load_scores<BEAM>(p, r, base, n, v);
+  const unsigned lmax = order_key(lane_best(v));
   const Red3 wr = wave_reduce(0u, (vm & 1u) ? lmax : ~0u, lmax);
   const unsigned km = unsigned(__popcll(__ballot((vm & 1u) && lmax == wr.hi)));
   if (lane_id() == 0)
