@@ -92,8 +92,17 @@ __device__ inline void float_to_delta(const float* x, unsigned* w, int n) {
   }
 }
 
+// Waves per SIMD asked of the compiler: at d = 128 with bf16 io the chain of five
+// records takes 144 registers when left alone, one workgroup per compute unit; held to
+// 128 (nothing spills) two fit, as for the shorter chains: 33.4 -> 27.6 us per launch at
+// 4 requests x 512 beams, 31.7 -> 26.4 at 8 x 256.  Longer chains spill 9 to 30 there:
+// six records 36.4 -> 34.4 at 4 x 512 but 33.2 -> 34.0 at 8 x 256, seven and eight slower.
+constexpr int replay_waves(int dk, int dv, int chain, bool bf16) {
+  return dk == 128 && dv == 128 && bf16 && chain == 5 ? 4 : 1;
+}
+
 template <int DK, int DV, int DVW, int NBLK, int CHAIN, bool BF16, bool FUSED>
-__global__ __launch_bounds__(4 * DK) void replay_kernel(ReplayParams p) {
+__global__ __launch_bounds__(4 * DK, replay_waves(DK, DV, CHAIN, BF16)) void replay_kernel(ReplayParams p) {
   constexpr int MB = DVW / DK;
   constexpr int NS = DV / DVW;
   constexpr int NW = DVW / (16 * MB);
