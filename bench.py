@@ -198,17 +198,20 @@ FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense fp32
 def prefill_chunked_flops(spec):
     """fp32 flops of onela_prefill_state_chunked as implemented: per chunk of
     C = 64 tokens and (request, value head), the lower ten of the sixteen
-    16 x 16 tiles of K K^T, the two products with the unit lower-triangular T
-    (row block a needs k < 16 (a + 1): 10/16 of the dense product), then the
-    scan's X = W' S^T and K^T D' over the whole chunk."""
+    16 x 16 tiles of K K^T, then, with bf16 keys, the scan's K S^T, T' D0 (T'
+    lower triangular: 10/16 of the dense product) and K^T D'; with fp32 keys
+    T (diag(beta gamma) K) and T (diag(beta) V) per chunk, then the scan's
+    X = W' S^T and K^T D'.  (Not counted: the transition matrices of a prompt
+    cut into segments.)"""
     C = 64
     nch = -(-spec.P // C)
     tri = 10 / 16
     per_chunk = (2 * C * C * spec.dk * tri          # K K^T
-                 + 2 * C * C * spec.dk * tri        # T (diag(beta gamma) K)
-                 + 2 * C * C * spec.dv * tri        # T (diag(beta) V)
-                 + 2 * C * spec.dk * spec.dv        # W' S^T
+                 + 2 * C * C * spec.dv * tri        # T' D0, or T (diag(beta) V)
+                 + 2 * C * spec.dk * spec.dv        # K S^T, or W' S^T
                  + 2 * C * spec.dk * spec.dv)       # K^T D'
+    if spec.io_dtype != "bf16":
+        per_chunk += 2 * C * C * spec.dk * tri      # T (diag(beta gamma) K)
     return spec.R * spec.HV * nch * per_chunk
 
 
@@ -652,12 +655,12 @@ def main():
                          "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                          "frac": flops / (chk_ms / 1e3) / 1e12 / FP32_MFMA_PEAK_TFLOPS,
                          "flops": flops,
-                         "count": "the fp32 products of the chunked method as computed: "
-                                  "K K^T, T.(diag(beta gamma) K), T.(diag(beta) V) per "
-                                  "chunk, W' S^T and K^T D' per chunk and 16-row block "
-                                  "(with bf16 keys the products with T and K^T D' run as "
-                                  "exact products of bf16 parts on the bf16 instruction; "
-                                  "counted once, as fp32 products)"},
+                         "count": "the products of the chunked method as computed, each "
+                                  "counted once as an fp32 product: K K^T per chunk, then "
+                                  "K S^T, T' D0 and K^T D' (fp32 keys: T.(diag(beta gamma) "
+                                  "K), T.(diag(beta) V), W' S^T and K^T D'); with bf16 keys "
+                                  "they run as three or six products of bf16 parts on the "
+                                  "bf16 instruction"},
             "note": "onela_prefill_state (token by token) vs onela_prefill_state_chunked "
                     "(64-token chunks); setup work, not part of `value`"}
         log(f"[bench] prefill {spec.P} tokens: sequential {seq_ms:.2f} ms, chunked {chk_ms:.3f} ms")

@@ -86,7 +86,7 @@ size_t prefill_chunked_workspace_bytes(const Shape& s, int prompt_len) {
 // at d_k <= 64, by their LDS).  A chunk takes about 4 us there, the launch that
 // chains n segments about 4 + 1.5 (n - 1) us (both measured at 16 heads, d = 128),
 // and every segment but the first also carries its transition matrix, so segments
-// pay only while workgroups are missing: 16 heads x 64 chunks 8 segments, 42 + 13 us
+// pay only while workgroups are missing: 16 heads x 64 chunks 8 segments, 42 + 12 us
 // (4: 66 + 7; 6: 51 + 10); 64 heads x 32 chunks 2, 75 + 8 (4: 83 + 14); 256 heads none.
 int prefill_segments(const Shape& s, int nch) {
   if (nch < 8 || s.cus <= 0) return 1;

@@ -25,7 +25,7 @@
 //     where the chip would otherwise be idle;
 //   prefill_combine_kernel: chains the segments (only with more than one).
 // Measured (one MI355X, 16 heads, d = 128; the launches by rocprofv3): 4096 tokens
-// factors 13 us, scan 42, combination 13, against 57 + 98 for the two launches of the
+// factors 13 us, scan 42, combination 11, against 57 + 98 for the two launches of the
 // form below; 16 requests x 1000 tokens 36 + 80 against 229 + 207.
 //
 // fp32 keys and values:

@@ -46,7 +46,8 @@ def short_name(name: str) -> str:
         return (f"decode_kernel<{mode}, d={dk}, chain={chain}, "
                 f"{'bf16' if bf16 == 'true' else 'f32'}{records}>")
     for k in ("resolve_kernel", "append_kernel", "prefill_kernel", "prefill_chunk_kernel",
-              "prefill_scan_kernel", "fullstate_kernel", "clear_status_kernel"):
+              "prefill_factor_kernel", "prefill_scan_kernel", "prefill_scan_f32_kernel",
+              "prefill_combine_kernel", "fullstate_kernel", "clear_status_kernel"):
         if k in name:
             return k
     m = re.search(r"(select_\w+_kernel)(<[^>]*>)?", name)
