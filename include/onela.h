@@ -228,15 +228,19 @@ onela_status_t onela_prefill_state(const onela_config_t* cfg, int32_t prompt_len
  * Same result as onela_prefill_state (Eq. 1 from S = 0 over the prompt, fp32
  * state), computed in chunks of 64 tokens: per chunk, the correction terms
  * delta_t of Eq. 2 solve a unit lower-triangular 64 x 64 system whose
- * matrices depend only on the chunk's own tokens (formed for all chunks in
+ * matrix depends only on the chunk's own tokens (formed for all chunks in
  * parallel); a second launch then carries the state across the chunks in
  * order, on the matrix cores (fp32 products, and for bf16 keys exact products
- * of bf16 parts).  Inputs and output as for onela_prefill_state.
+ * of bf16 parts), with bf16 keys cut into segments that run at once where few
+ * heads would leave the chip idle and that a third launch chains.  Inputs and
+ * output as for onela_prefill_state.
  * Workspace: onela_prefill_workspace_bytes(cfg, prompt_len) bytes (0 for an
  * empty prompt, or for an invalid cfg), 256-byte aligned, owned by the caller
- * and used only by the enqueued work: per (request, value head, chunk) the
- * fp32 matrices W [64][d_k], Kt^T [d_k][64], U^T [d_v][64] (in the order the
- * scan loads them) and the chunk's decay (16 copies).
+ * and used only by the enqueued work: with fp32 keys, per (request, value head,
+ * chunk) the fp32 matrices W [64][d_k], Kt^T [d_k][64], U^T [d_v][64] (in the order
+ * the scan loads them) and the chunk's decay (16 copies); with bf16 keys the
+ * chunks' split triangular factors and decays and the segments' states and
+ * transition matrices, in the same space.
  * Errors: ONELA_EINVAL, ONELA_ECAPACITY (workspace too small), ONELA_EHIP. */
 size_t onela_prefill_workspace_bytes(const onela_config_t* cfg, int32_t prompt_len);
 onela_status_t onela_prefill_state_chunked(const onela_config_t* cfg, int32_t prompt_len,
