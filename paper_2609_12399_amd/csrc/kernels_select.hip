@@ -2193,10 +2193,14 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p)
   for (; over != 0ull; over &= over - 1ull) {  // a chunk's exact top W of its survivors
     const unsigned c = chunk_at(unsigned(__builtin_ctzll(over))), bound = bound_of(c);
     const unsigned base = c * unsigned(kSelectChunk);
+    // (the mask that overflowed, as the cut needs at least W: a bound of +0 keeps the -0s
+    // as scores, and compared as keys fewer than W may be left)
     unsigned key[kNI];
-    unsigned keep = load_raw<BEAM>(p, r, base, min(p.N - base, unsigned(kSelectChunk)), key);
+    const unsigned vmask =
+        load_scores<BEAM>(p, r, base, min(p.N - base, unsigned(kSelectChunk)), val);
+    unsigned keep = kept_mask(val, vmask, bound);
 #pragma unroll
-    for (int i = 0; i < kNI; ++i) keep &= ~(unsigned(key[i] < bound) << i);
+    for (int i = 0; i < kNI; ++i) key[i] = order_key(val[i]);
     __syncthreads();
     keep = cut_mask(sh, key, keep, find_cut(sh, key, keep, p.W));
     const unsigned total = replan_sparse(keep, sh);

@@ -126,6 +126,32 @@ def test_select_one_pass_many_tied_survivors(tied_slots):
     assert np.array_equal(sc.cpu().numpy()[0].view(np.int32), osc.view(np.int32))
 
 
+@pytest.mark.parametrize("at", ["minus_zero", "plus_zero"])
+@pytest.mark.parametrize("R,P,V,W", [(1, 300, SELECT_CODEBOOK, 64), (3, 500, 3001, 200),
+                                     (2, 1024, 4096, 1024), (2, 37, 1001, 300)],
+                         ids=["one_pass", "stream", "two_pass", "tree"])
+def test_select_signed_zeros_at_the_bound(R, P, V, W, at):
+    """-0.0 orders below +0.0, and a comparison of floats does not see it.
+    Nearly all scores are -0.0, with fewer than W numbers above them in every
+    chunk of 16384, so that the chunks' slots overflow with zeros: either the
+    bound is -0.0, or every chunk has W / 4 +0.0 and the bound is +0.0."""
+    import torch
+    from paper_2609_12399_amd.runner import BeamSelector
+    rng = np.random.default_rng(11)
+    logp = np.full((R, P * V), -0.0, dtype=np.float32)
+    for r in range(R):
+        for base in range(0, P * V, 16384):
+            q = base + rng.permutation(min(16384, P * V - base))
+            logp[r, q[:3]] = rng.random(min(3, q.size)) + 0.5
+            if at == "plus_zero":
+                logp[r, q[3:3 + W // 4]] = 0.0
+    logp = logp.reshape(R, P, V)
+    print(f"signed zeros R={R} W_prev={P} V={V} W={W} {at}", flush=True)
+    par, tok, sc = BeamSelector(R, P, V, W)(torch.from_numpy(logp).cuda(), None)
+    torch.cuda.synchronize()
+    _check(logp, None, W, par.cpu().numpy(), tok.cpu().numpy(), sc.cpu().numpy())
+
+
 def test_select_all_equal_keeps_lowest_indices():
     import torch
     from paper_2609_12399_amd.runner import BeamSelector
