@@ -1605,13 +1605,49 @@ __device__ inline unsigned long long composite(uint2 e) {
   return (static_cast<unsigned long long>(e.x) << 32) | unsigned(~e.y);
 }
 
+// Writes out each of the m composites in `c` (LDS, readable up to the next multiple of
+// 512) whose place among them is below W.  This workgroup's share is the composites
+// part, part + nparts, ...; a composite's place is the number of larger ones.  A wave
+// counts for two at once over interleaved pairs of positions, four pairs per lane in
+// flight (the positions at or beyond m are not counted).
+template <bool BEAM>
+__device__ inline void direct_rank_emit(const SelectParams& p, unsigned r,
+                                        const unsigned long long* c, unsigned m, unsigned part,
+                                        unsigned nparts) {
+  const unsigned lane = lane_id(), w = threadIdx.x >> 6;
+  for (unsigned k = 0;; k += 2u * kWaves) {
+    if (part + nparts * k >= m) break;  // workgroup-uniform
+    const unsigned q0 = part + nparts * (k + w), q1 = part + nparts * (k + kWaves + w);
+    const unsigned long long x0 = c[q0 < m ? q0 : 0u], x1 = c[q1 < m ? q1 : 0u];
+    unsigned c0 = 0u, c1 = 0u;
+    for (unsigned j0 = 0; j0 < m; j0 += 512u) {
+      ulonglong2 y[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        y[i] = *reinterpret_cast<const ulonglong2*>(&c[j0 + 128u * unsigned(i) + 2u * lane]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned j = j0 + 128u * unsigned(i) + 2u * lane;
+        const bool v0 = j < m, v1 = j + 1u < m;
+        c0 += unsigned(v0 && y[i].x > x0) + unsigned(v1 && y[i].y > x0);
+        c1 += unsigned(v0 && y[i].x > x1) + unsigned(v1 && y[i].y > x1);
+      }
+    }
+    const Red3 r0 = wave_reduce(c0, 0u, 0u), r1 = wave_reduce(c1, 0u, 0u);
+    if (lane == 0u && q0 < m && r0.sum < p.W) emit_pick<BEAM>(p, r, r0.sum, x0);
+    if (lane == 1u && q1 < m && r1.sum < p.W) emit_pick<BEAM>(p, r, r1.sum, x1);
+  }
+}
+
 // Writes out each of the m (<= kRankCap) composites in `c` (LDS) whose
 // place among them -- the number of larger ones -- is below W.  The
 // composites are grouped by a 2048-bin histogram of key - lo (bins in
 // descending key order, so a bin's first position is the number of
 // composites in the bins above it); a composite's place is then its bin's
 // first position plus the larger composites of its own bin, which is
-// usually a handful (all of them only when the keys are nearly equal).
+// usually a handful.  Where one bin holds an eighth of them or more (tied keys) they are
+// compared directly instead (one request, 512 x 8192 -> 512: 1536 equal survivors 24.2 us
+// per call against 29.8 through the bins, 3072 34.4 against 52.9).
 template <bool BEAM>
 __device__ inline void bucket_rank_emit(const SelectParams& p, OnePassShared& u, unsigned r,
                                         const unsigned long long* c, unsigned m,
@@ -1626,6 +1662,10 @@ __device__ inline void bucket_rank_emit(const SelectParams& p, OnePassShared& u,
   }
   const Red3 rr = block_reduce(sh, 0u, lo, hi);
   if (m == 0u) return;
+  if (rr.lo == rr.hi) {  // (the test below, without a histogram of one bin)
+    direct_rank_emit<BEAM>(p, r, c, m, part, nparts);
+    return;
+  }
   const int width = bit_width(rr.hi - rr.lo);
   const int shift = width > 11 ? width - 11 : 0;
   auto bin_of = [&](unsigned long long x) { return (unsigned(x >> 32) - rr.lo) >> shift; };
@@ -1637,11 +1677,22 @@ __device__ inline void bucket_rank_emit(const SelectParams& p, OnePassShared& u,
     const uint4 h = reinterpret_cast<const uint4*>(sh.hist)[kThreads - 1 - t];
     const unsigned sum = h.x + h.y + h.z + h.w;
     const unsigned inc = wave_scan(sum);
-    if (lane == 63) sh.red[0][w] = inc;
+    const Red3 most = wave_reduce(0u, 0u, max(max(h.x, h.y), max(h.z, h.w)));
+    if (lane == 63) {
+      sh.red[0][w] = inc;
+      sh.red[1][w] = most.hi;
+    }
     __syncthreads();
-    unsigned above = inc - sum;
+    unsigned above = inc - sum, largest = 0u;
 #pragma unroll
-    for (int w2 = 0; w2 < kWaves; ++w2) above += unsigned(w2) < w ? sh.red[0][w2] : 0u;
+    for (int w2 = 0; w2 < kWaves; ++w2) {
+      above += unsigned(w2) < w ? sh.red[0][w2] : 0u;
+      largest = max(largest, sh.red[1][w2]);
+    }
+    if (8u * largest >= m) {  // workgroup-uniform
+      direct_rank_emit<BEAM>(p, r, c, m, part, nparts);
+      return;
+    }
     const unsigned b0 = 2047u - 4u * t;
     u.bstart[b0] = above;
     u.bstart[b0 - 1u] = above + h.w;
@@ -1780,8 +1831,10 @@ __device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, uns
 // pass of the exact top-W cut.
 constexpr int kSpecEntries = 32;     // slot entries loaded with the counts
 constexpr int kSpecRows = kThreads / 32;  // 32 slots per row of loads (8 waves x 4 slots)
-// Survivors ranked by direct comparison; through the key histogram beyond (about 1200
-// survivors at 8 requests: 10.5 us compared directly, 7.4 through the histogram).
+// Survivors ranked by direct comparison; through the key histogram beyond, unless they
+// are tied.  The line at 1024 against one at 2048: about 1200 survivors at 8 requests (32
+// workgroups each) 7.4 us per launch against 10.5, 512 x 8192 -> 800 (64 workgroups) 18.7 us
+// per call against 19.3, 16 requests of 256 x 8192 -> 256 with a skewed vocabulary 75.8 against 83.4.
 constexpr int kBruteRankMax = 1024;
 // With TWO (at most half as many slots as the rows hold) two rows of loads cover each
 // slot, 64 entries: the streaming form leaves more survivors in a chunk.
@@ -1883,33 +1936,7 @@ __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, un
     bucket_rank_emit<BEAM>(p, u, r, u.all, total, part, nparts);
     return;
   }
-  // this workgroup's share: survivors part, part + nparts, ...; a survivor's
-  // place is the number of larger composites.  A wave counts for two
-  // survivors at once over interleaved pairs of positions, four pairs per
-  // lane in flight (positions up to total + 511 < kRankCap are read; the ones
-  // at or beyond total are not counted).
-  for (unsigned k = 0;; k += 2u * kWaves) {
-    if (part + nparts * k >= total) break;  // workgroup-uniform
-    const unsigned q0 = part + nparts * (k + w), q1 = part + nparts * (k + kWaves + w);
-    const unsigned long long x0 = u.all[q0 < total ? q0 : 0u], x1 = u.all[q1 < total ? q1 : 0u];
-    unsigned c0 = 0u, c1 = 0u;
-    for (unsigned j0 = 0; j0 < total; j0 += 512u) {
-      ulonglong2 y[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        y[i] = *reinterpret_cast<const ulonglong2*>(&u.all[j0 + 128u * unsigned(i) + 2u * lane]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const unsigned j = j0 + 128u * unsigned(i) + 2u * lane;
-        const bool v0 = j < total, v1 = j + 1u < total;
-        c0 += unsigned(v0 && y[i].x > x0) + unsigned(v1 && y[i].y > x0);
-        c1 += unsigned(v0 && y[i].x > x1) + unsigned(v1 && y[i].y > x1);
-      }
-    }
-    const Red3 r0 = wave_reduce(c0, 0u, 0u), r1 = wave_reduce(c1, 0u, 0u);
-    if (lane == 0u && q0 < total && r0.sum < p.W) emit_pick<BEAM>(p, r, r0.sum, x0);
-    if (lane == 1u && q1 < total && r1.sum < p.W) emit_pick<BEAM>(p, r, r1.sum, x1);
-  }
+  direct_rank_emit<BEAM>(p, r, u.all, total, part, nparts);
 }
 
 template <bool BEAM>

@@ -98,16 +98,18 @@ def test_select_matches_oracle(name, R, P, V, W, kind, with_beam):
             f"request {r}: scores differ"
 
 
-@pytest.mark.parametrize("tied_slots", [6, 32], ids=["histogram_ranked", "exact_cut"])
-def test_select_one_pass_many_tied_survivors(tied_slots):
+@pytest.mark.parametrize("tied_slots,better", [(2, 0), (3, 0), (6, 0), (6, 300), (12, 0), (14, 200),
+                                               (32, 0)])
+def test_select_one_pass_many_tied_survivors(tied_slots, better):
     """Ties held by the first lane of every wave (a chunk's candidate at slot
     i of lane t sits at position 512 i + t): each wave then guarantees one
     candidate at the tied key, so all chunks up to c* (the 64th) keep every
-    tied candidate of theirs, 64 x 8 x tied_slots survivors -- more than the
-    final stage ranks by direct comparison (6 slots: 3072, ranked through the
-    key histogram) or more than it stages at all (32 slots: 16384, the exact
-    top-W cut over the slots).  The result is the W tied candidates with the
-    lowest flat indices."""
+    tied candidate of theirs, 64 x 8 x tied_slots survivors: 1024 are
+    ranked by direct comparison, more too as far as they are staged, with
+    `better` distinct scores above them or none (the histogram's largest bin
+    holds the ties); 16384 are more than the final stage stages at all (the
+    exact top-W cut over the slots).  The result is the `better` scores and the
+    tied candidates with the lowest flat indices."""
     import torch
     from paper_2609_12399_amd.runner import BeamSelector
     R, P, V, W = 1, 512, SELECT_CODEBOOK, 512
@@ -115,8 +117,10 @@ def test_select_one_pass_many_tied_survivors(tied_slots):
     logp = (-1.0 - rng.random(P * V, dtype=np.float32)).astype(np.float32)
     q = np.arange(P * V)
     logp[(q % 64 == 0) & ((q % 16384) // 512 < tied_slots)] = 0.0
+    up = rng.permutation(P * V)[:better]
+    logp[up] = 1.0 + rng.random(better, dtype=np.float32)
     logp = logp.reshape(R, P, V)
-    print(f"one-pass tied survivors: {64 * 8 * tied_slots}", flush=True)
+    print(f"one-pass tied survivors: {64 * 8 * tied_slots}, {better} above", flush=True)
     sel = BeamSelector(R, P, V, W)
     par, tok, sc = sel(torch.from_numpy(logp).cuda(), None)
     torch.cuda.synchronize()
