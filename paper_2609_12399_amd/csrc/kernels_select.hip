@@ -59,6 +59,7 @@ constexpr int kMaxSlotsPerGroup = 256;
 constexpr int kRankCap = 4096;                // survivors the rank kernel orders
 constexpr int kRankPer = kThreads / 16;       // survivors ranked per workgroup (16 lanes each)
 constexpr int kRankBlocks = kRankCap / kRankPer;
+constexpr int kPlaceCap = 7168;               // survivors the placing kernel orders
 constexpr int kOnePassRankMax = 1024;         // widest result of the one-pass path
 constexpr int kOnePassFinalParts = 64;       // workgroups per request placing survivors (at most)
 constexpr double kStreamKeep = 1500.0;       // survivors the streaming form may expect
@@ -453,14 +454,17 @@ struct Cut {
 // keys.  Radix passes of up to 11 bits run over key - lo (lo: the smallest
 // valid key), from its top bit down, and stop early when the boundary bin is
 // taken whole.
-__device__ inline Cut find_cut(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
-                               unsigned need) {
+// key(i): the key of slot i.  Unless EXACT any cut that keeps need to most keys will do
+// (usually the first pass finds one).
+template <bool EXACT, typename KeyOf>
+__device__ inline Cut find_cut_of(SelShared& sh, KeyOf&& key, unsigned vm, unsigned need,
+                                  unsigned most) {
   unsigned lo = ~0u, hi = 0u;
 #pragma unroll
   for (int i = 0; i < kNI; ++i)
     if ((vm >> i) & 1u) {
-      lo = min(lo, key[i]);
-      hi = max(hi, key[i]);
+      lo = min(lo, key(i));
+      hi = max(hi, key(i));
     }
   const Red3 r = block_reduce(sh, 0u, lo, hi);
   if (r.lo == r.hi) return Cut{r.lo, need, ~0u};  // all equal: ties by position
@@ -475,28 +479,34 @@ __device__ inline Cut find_cut(SelShared& sh, const unsigned (&key)[kNI], unsign
     const unsigned mask = (1u << bits) - 1u;
 #pragma unroll
     for (int i = 0; i < kNI; ++i) {
-      const unsigned rel = key[i] - r.lo;
+      const unsigned rel = key(i) - r.lo;
       const bool act = ((vm >> i) & 1u) && shr(rel, shift + bits) == prefix;
       hist_add(sh.hist, (rel >> shift) & mask, act);
     }
     __syncthreads();
     find_bin(sh, need);
     prefix = (prefix << bits) | sh.digit;
+    if constexpr (!EXACT) most -= need - sh.need;  // (less the keys above the bin)
     need = sh.need;
     const unsigned cnt = sh.cnt;
-    if (cnt == need) return Cut{r.lo + (prefix << shift), 0u, 0u};
+    if (EXACT ? cnt == need : cnt <= most) return Cut{r.lo + (prefix << shift), 0u, 0u};
     if (shift == 0) return Cut{r.lo + prefix, need, cnt};
   }
 }
 
+__device__ inline Cut find_cut(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
+                               unsigned need) {
+  return find_cut_of<true>(sh, [&](int i) { return key[i]; }, vm, need, need);
+}
+
 // Selection mask of a cut (bit i: slot i); ties resolved in position order.
-__device__ inline unsigned cut_mask(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
-                                    const Cut& c) {
+template <typename KeyOf>
+__device__ inline unsigned cut_mask_of(SelShared& sh, KeyOf&& key, unsigned vm, const Cut& c) {
   unsigned ge = 0u, eq = 0u;
 #pragma unroll
   for (int i = 0; i < kNI; ++i) {
-    ge |= unsigned(c.take == 0u ? key[i] >= c.tau : key[i] > c.tau) << i;
-    eq |= unsigned(key[i] == c.tau) << i;
+    ge |= unsigned(c.take == 0u ? key(i) >= c.tau : key(i) > c.tau) << i;
+    eq |= unsigned(key(i) == c.tau) << i;
   }
   ge &= vm;
   if (c.take == 0u) return ge;
@@ -510,6 +520,11 @@ __device__ inline unsigned cut_mask(SelShared& sh, const unsigned (&key)[kNI], u
     eq &= ~drop;
   }
   return ge | eq;
+}
+
+__device__ inline unsigned cut_mask(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
+                                    const Cut& c) {
+  return cut_mask_of(sh, [&](int i) { return key[i]; }, vm, c);
 }
 
 // ---- loads -----------------------------------------------------------------
@@ -1276,7 +1291,7 @@ __global__ __launch_bounds__(kThreads) void select_rank_kernel(SelectParams p) {
 //      largest key;
 //   4. the final kernel places the survivors: each one's place is the number
 //      of larger (key, ~index) composites, counted directly (up to
-//      kBruteRankMax survivors) or through a key histogram (up to kRankCap;
+//      kBruteRankMax survivors) or through a key histogram (up to kPlaceCap;
 //      staged in LDS by each of the request's fparts workgroups, which place
 //      a share each); with more,
 //      one workgroup finds their exact top W first (radix cut, ties in index
@@ -1589,9 +1604,9 @@ __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelSha
 struct OnePassShared {
   SelShared sh;
   unsigned start[kSelectMaxGatherSlots + 1];      // slot s holds positions [start[s], start[s+1])
-  alignas(16) unsigned long long all[kRankCap + 128];  // survivors' composites, when they fit
+  alignas(16) unsigned long long all[kPlaceCap + 128];  // survivors' composites, when they fit
                                                        // (+ a spare pair per lane)
-  alignas(16) unsigned long long buck[kRankCap];  // the same, grouped by key bin
+  alignas(16) unsigned long long buck[kPlaceCap];  // the same, grouped by key bin
   alignas(16) unsigned long long top[kOnePassRankMax];  // the exact top W
   unsigned bstart[2048];                          // first position of each key bin in buck
   unsigned ntop;
@@ -1639,19 +1654,19 @@ __device__ inline void direct_rank_emit(const SelectParams& p, unsigned r,
   }
 }
 
-// Writes out each of the m (<= kRankCap) composites in `c` (LDS) whose
+// Writes out each of the m (<= kPlaceCap) composites in `c` (LDS) whose
 // place among them -- the number of larger ones -- is below W.  The
 // composites are grouped by a 2048-bin histogram of key - lo (bins in
 // descending key order, so a bin's first position is the number of
 // composites in the bins above it); a composite's place is then its bin's
 // first position plus the larger composites of its own bin, which is
 // usually a handful.  Where one bin holds an eighth of them or more (tied keys) they are
-// compared directly instead (one request, 512 x 8192 -> 512: 1536 equal survivors 24.2 us
-// per call against 29.8 through the bins, 3072 34.4 against 52.9).
+// to be compared directly instead: false, with nothing written (one request, 512 x 8192 ->
+// 512: 1536 equal survivors 24.2 us per call against 29.8 through the bins, 3072 34.4 against 52.9).
 template <bool BEAM>
-__device__ inline void bucket_rank_emit(const SelectParams& p, OnePassShared& u, unsigned r,
+__device__ inline bool bucket_rank_emit(const SelectParams& p, OnePassShared& u, unsigned r,
                                         const unsigned long long* c, unsigned m,
-                                        unsigned part = 0u, unsigned nparts = 1u) {
+                                        unsigned part, unsigned nparts) {
   SelShared& sh = u.sh;
   const unsigned t = threadIdx.x, lane = lane_id(), w = t >> 6;
   unsigned lo = ~0u, hi = 0u;
@@ -1661,11 +1676,8 @@ __device__ inline void bucket_rank_emit(const SelectParams& p, OnePassShared& u,
     hi = max(hi, k);
   }
   const Red3 rr = block_reduce(sh, 0u, lo, hi);
-  if (m == 0u) return;
-  if (rr.lo == rr.hi) {  // (the test below, without a histogram of one bin)
-    direct_rank_emit<BEAM>(p, r, c, m, part, nparts);
-    return;
-  }
+  if (m == 0u) return true;
+  if (rr.lo == rr.hi) return false;  // (the test below, without a histogram of one bin)
   const int width = bit_width(rr.hi - rr.lo);
   const int shift = width > 11 ? width - 11 : 0;
   auto bin_of = [&](unsigned long long x) { return (unsigned(x >> 32) - rr.lo) >> shift; };
@@ -1677,22 +1689,19 @@ __device__ inline void bucket_rank_emit(const SelectParams& p, OnePassShared& u,
     const uint4 h = reinterpret_cast<const uint4*>(sh.hist)[kThreads - 1 - t];
     const unsigned sum = h.x + h.y + h.z + h.w;
     const unsigned inc = wave_scan(sum);
-    const Red3 most = wave_reduce(0u, 0u, max(max(h.x, h.y), max(h.z, h.w)));
+    const unsigned long long big = __ballot(8u * max(max(h.x, h.y), max(h.z, h.w)) >= m);
     if (lane == 63) {
       sh.red[0][w] = inc;
-      sh.red[1][w] = most.hi;
+      sh.red[1][w] = unsigned(big != 0ull);
     }
     __syncthreads();
-    unsigned above = inc - sum, largest = 0u;
+    unsigned above = inc - sum, tied = 0u;
 #pragma unroll
     for (int w2 = 0; w2 < kWaves; ++w2) {
       above += unsigned(w2) < w ? sh.red[0][w2] : 0u;
-      largest = max(largest, sh.red[1][w2]);
+      tied |= sh.red[1][w2];
     }
-    if (8u * largest >= m) {  // workgroup-uniform
-      direct_rank_emit<BEAM>(p, r, c, m, part, nparts);
-      return;
-    }
+    if (tied != 0u) return false;  // workgroup-uniform
     const unsigned b0 = 2047u - 4u * t;
     u.bstart[b0] = above;
     u.bstart[b0 - 1u] = above + h.w;
@@ -1727,17 +1736,18 @@ __device__ inline void bucket_rank_emit(const SelectParams& p, OnePassShared& u,
     cnt += dppu<0x140>(cnt);  // row_mirror
     if (sub == 0u && q < m && s0 + cnt < p.W) emit_pick<BEAM>(p, r, s0 + cnt, x);
   }
+  return true;
 }
 
 // The exact top W (W <= kOnePassRankMax <= n) of the n survivors of request
-// r, read through get(q) in position (= index) order: radix passes of up to
+// r, read through get(q) in position order (index order too, but for the
+// streaming form): radix passes of up to
 // 11 bits over key - lo find the cut (every key above tau is in, and of the
-// keys equal to tau the first `take` by position, or all keys >= tau when
-// take = 0), the kept composites are collected in LDS, and each is placed by
-// the number of larger ones.
-template <bool BEAM, typename Get>
-__device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, unsigned r,
-                                    unsigned n, Get&& get) {
+// keys equal to tau the first `take` by index, or all keys >= tau when
+// take = 0), and the kept composites are collected in u.top.  Returns their number.
+template <typename Get>
+__device__ inline unsigned onepass_topw(const SelectParams& p, OnePassShared& u, unsigned n,
+                                        Get&& get) {
   const unsigned t = threadIdx.x, lane = lane_id(), w = t >> 6;
   SelShared& sh = u.sh;
   const unsigned W = p.W;
@@ -1786,6 +1796,35 @@ __device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, uns
       }
     }
   }
+  // The streaming form's slots are not in index order: of the keys equal to tau
+  // the first `take` by index are those whose complemented index is at least `low`
+  // (radix passes over it, as over the keys).
+  unsigned low = ~0u;
+  const bool by_index = take > 0u && p.groups != 0u;
+  if (by_index) {
+    unsigned prefix = 0u, need = take;
+    int shift = 32;
+#pragma nounroll
+    for (;;) {
+      const int bits = shift < 11 ? shift : 11;
+      shift -= bits;
+      reinterpret_cast<uint4*>(sh.hist)[t] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+      const unsigned mask = (1u << bits) - 1u;
+      for (unsigned q = t; q < n; q += kThreads) {
+        const unsigned long long c = get(q);
+        const unsigned x = unsigned(c);
+        if (unsigned(c >> 32) == tau && shr(x, shift + bits) == prefix)
+          atomicAdd(&sh.hist[(x >> shift) & mask], 1u);
+      }
+      __syncthreads();
+      find_bin(sh, need);
+      prefix = (prefix << bits) | sh.digit;
+      need = sh.need;
+      if (sh.cnt == need || shift == 0) break;  // (indices differ: at shift 0 the bin has one)
+    }
+    low = prefix << shift;
+  }
   if (t == 0) u.ntop = 0u;
   __syncthreads();
   unsigned eq_before = 0u;  // keys equal to tau at earlier positions
@@ -1795,7 +1834,9 @@ __device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, uns
     const unsigned long long c = valid ? get(q) : 0ull;
     const unsigned k = unsigned(c >> 32);
     bool sel = valid && (all_in || (take == 0u ? k >= tau : k > tau));
-    if (take > 0u) {  // workgroup-uniform
+    if (by_index) {
+      sel = sel || (valid && k == tau && unsigned(c) >= low);
+    } else if (take > 0u) {  // workgroup-uniform
       const bool eq = valid && k == tau;
       const unsigned long long be = __ballot(eq);
       if (lane == 0) sh.red[0][w] = unsigned(__popcll(be));
@@ -1817,7 +1858,7 @@ __device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, uns
     }
   }
   __syncthreads();
-  bucket_rank_emit<BEAM>(p, u, r, u.top, min(u.ntop, unsigned(kOnePassRankMax)));
+  return min(u.ntop, unsigned(kOnePassRankMax));
 }
 
 // Final stage of request r in one of its nparts workgroups (every chunk's
@@ -1826,7 +1867,7 @@ __device__ inline void onepass_topw(const SelectParams& p, OnePassShared& u, uns
 // entries (kSpecEntries or twice that) of every slot (coalesced: a wave instruction covers 4
 // slots, 16 lanes x 16 bytes each), which holds every survivor of most chunks;
 // the survivors beyond them (a chunk holding many) are loaded by whole
-// waves, one such chunk per wave at a time.  Up to kRankCap survivors are
+// waves, one such chunk per wave at a time.  Up to kPlaceCap survivors are
 // staged in LDS in position order; more are read from the slots on every
 // pass of the exact top-W cut.
 constexpr int kSpecEntries = 32;     // slot entries loaded with the counts
@@ -1882,7 +1923,11 @@ __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, un
   if (t == 0) u.start[kThreads] = total;
   if (cnt > spec) u.over[atomicAdd(&u.nover, 1u)] = t;
   __syncthreads();
-  if (total > unsigned(kRankCap)) {  // rare (heavy ties, or a bound that came late)
+  const unsigned long long* c = u.all;  // what is placed, and how many
+  unsigned m = total;
+  const bool cut = total > unsigned(kPlaceCap);
+  if (cut) {  // rare (heavy ties, or a bound that came late)
+    if (part != 0u) return;
     // position q lies in the last slot whose start is <= q
     auto from_slots = [&](unsigned q) -> unsigned long long {
       unsigned lo = 0u, hi = ns;  // start[lo] <= q < start[hi]
@@ -1893,50 +1938,50 @@ __device__ inline void onepass_final(const SelectParams& p, OnePassShared& u, un
       }
       return composite(slots[size_t(lo) * p.cap + (q - u.start[lo])]);
     };
-    if (part == 0u) onepass_topw<BEAM>(p, u, r, total, from_slots);
-    return;
-  }
-  // starts of the rows' slots first (c < kThreads), then the writes of the
-  // rows that hold chunks, unconditional: an entry past its slot's count
-  // goes to a lane's own spare place after the staged range
-  unsigned s0[kSpecRows], nn[kSpecRows];
+    m = onepass_topw(p, u, total, from_slots);
+    c = u.top;
+    nparts = 1u;
+  } else {
+    // starts of the rows' slots first (c < kThreads), then the writes of the
+    // rows that hold chunks, unconditional: an entry past its slot's count
+    // goes to a lane's own spare place after the staged range
+    unsigned s0[kSpecRows], nn[kSpecRows];
 #pragma unroll
-  for (int i = 0; i < kSpecRows; ++i) {  // (no branch around reads: see the loads above)
-    const unsigned c = slot_of(i);
-    s0[i] = u.start[c];
-    nn[i] = u.start[c + 1] - s0[i];  // 0 beyond the request's chunks
-  }
-  const unsigned spare = unsigned(kRankCap) + 2u * lane;
-#pragma unroll
-  for (int i = 0; i < kSpecRows; ++i)
-    if (unsigned(i % ROWS1) * 32u < ns) {
-      const unsigned j = entry_of(i);
-      u.all[j < nn[i] ? s0[i] + j : spare] = composite(make_uint2(ent[i].x, ent[i].y));
-      u.all[j + 1u < nn[i] ? s0[i] + j + 1u : spare + 1u] = composite(make_uint2(ent[i].z, ent[i].w));
+    for (int i = 0; i < kSpecRows; ++i) {  // (no branch around reads: see the loads above)
+      const unsigned c = slot_of(i);
+      s0[i] = u.start[c];
+      nn[i] = u.start[c + 1] - s0[i];  // 0 beyond the request's chunks
     }
-  for (unsigned i = w; i < u.nover; i += kWaves) {  // wave-uniform
-    const unsigned c = u.over[i], s0 = u.start[c], n = u.start[c + 1] - s0;
-    const uint2* sl = slots + size_t(c) * p.cap;
-    for (unsigned j0 = spec; j0 < n; j0 += 512u) {  // 8 loads per lane in flight
-      uint2 v[8];
+    const unsigned spare = unsigned(kPlaceCap) + 2u * lane;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const unsigned jj = j0 + 64u * unsigned(k) + lane;
-        v[k] = sl[jj < n ? jj : n - 1u];
+    for (int i = 0; i < kSpecRows; ++i)
+      if (unsigned(i % ROWS1) * 32u < ns) {
+        const unsigned j = entry_of(i);
+        u.all[j < nn[i] ? s0[i] + j : spare] = composite(make_uint2(ent[i].x, ent[i].y));
+        u.all[j + 1u < nn[i] ? s0[i] + j + 1u : spare + 1u] = composite(make_uint2(ent[i].z, ent[i].w));
       }
+    for (unsigned i = w; i < u.nover; i += kWaves) {  // wave-uniform
+      const unsigned c = u.over[i], s0 = u.start[c], n = u.start[c + 1] - s0;
+      const uint2* sl = slots + size_t(c) * p.cap;
+      for (unsigned j0 = spec; j0 < n; j0 += 512u) {  // 8 loads per lane in flight
+        uint2 v[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const unsigned jj = j0 + 64u * unsigned(k) + lane;
-        if (jj < n) u.all[s0 + jj] = composite(v[k]);
+        for (int k = 0; k < 8; ++k) {
+          const unsigned jj = j0 + 64u * unsigned(k) + lane;
+          v[k] = sl[jj < n ? jj : n - 1u];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const unsigned jj = j0 + 64u * unsigned(k) + lane;
+          if (jj < n) u.all[s0 + jj] = composite(v[k]);
+        }
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
-  if (total > unsigned(kBruteRankMax)) {
-    bucket_rank_emit<BEAM>(p, u, r, u.all, total, part, nparts);
+  if ((cut || m > unsigned(kBruteRankMax)) && bucket_rank_emit<BEAM>(p, u, r, c, m, part, nparts))
     return;
-  }
-  direct_rank_emit<BEAM>(p, r, u.all, total, part, nparts);
+  direct_rank_emit<BEAM>(p, r, c, m, part, nparts);
 }
 
 template <bool BEAM>
@@ -2022,84 +2067,169 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
 
 // Streaming form, for calls with more chunks than workgroups fit the device:
 // p.groups workgroups per request (all resident, as above) take p.per consecutive
-// chunks each.  The chunk that a workgroup reads first, one in p.per of the request's,
-// serves as a sample (the first chunk of one workgroup, the last of the next, the
-// request's first and last among them, so that scores that fall or rise with the
-// beam show their best): its summaries form the bound (which holds for all candidates, since W of
-// the sample's reach it), while the next two chunks arrive, and these are filtered
-// as soon as it is there.  So every score is read once, and about p.per
-// times as many candidates survive as with a bound from all chunks.  Summaries
-// are taken per 16-lane row (SPC = 32) where they fit, because the sample has fewer
-// waves and the guaranteed counts need about three times W of them to be tight.
-//   Bound: the first chunk's round trip and the bound (about 12 us), then per
-// chunk a barrier-separated compaction by one workgroup per compute unit (8 x 256 x
-// 8192, 67 MB in four chunks per workgroup: 31.6 us; a plain read takes 10.5).  With
-// keys in place of scores 34.5 us; three chunks ahead in place of two 38 us (the
+// chunks each and read them in as many rounds, every score once.  The first round
+// serves as a sample: its summaries form the bound (which holds for all candidates, since
+// W of the sample's reach it) while the next two rounds' scores arrive, and
+// these are filtered as soon as it is there; about p.per times as many candidates
+// survive as with a bound from all of them.  Summaries are taken per 16-lane row
+// (SPC = 32) where they fit, because the sample has fewer waves and the
+// guaranteed counts need about three times W of them to be tight.
+//   Each round reads pieces of 64 candidates from all over the workgroup's
+// range (StreamRange), so that the sample has the same share of every beam and of
+// every part of the vocabulary, and a round that overflows its slot raises the
+// workgroup's bound for the ones after it.  With whole chunks as rounds, each cut by
+// itself, the sample missed the good candidates where these lay in certain
+// beams or tokens: 4 requests x 64 x 65536 -> 64 with the better tokens in the middle
+// half of the vocabulary took 112 us per call (now 32; two passes: 49), 8 x 256 x 8192 ->
+// 256 with steeply rising beam scores 101 (now 66; two passes: 76).
+//   Bound: the first round's round trip and the bound (about 12 us), then per
+// round a barrier-separated compaction by one workgroup per compute unit (8 x 256 x
+// 8192, 67 MB in four rounds per workgroup: 31.6 us; a plain read takes 10.5).  With
+// keys in place of scores 34.5 us; three rounds ahead in place of two 38 us (the
 // polls of the bound wait behind the loads: the vector memory counter retires in
 // order).
 
-// The log-probabilities of a chunk on their way: the beam scores are added when they
+// The range of a workgroup, [base, base + n) of its request, and its rounds.  It is cut
+// into pieces of 64 candidates, and these into rows of nc pieces, row 8 i + w for slot
+// i of wave w; round j reads the piece (turn(i) + j) mod nc of each row.
+// turn() changes every four slots and with the workgroup, so that rows of the score
+// matrix are not all sampled at the same tokens.  Within a round the index rises with
+// the position, as in a chunk.
+struct StreamRange {
+  unsigned base, n, nc, hg;
+  __device__ StreamRange(const SelectParams& p, unsigned g)
+      : base(g * p.per * unsigned(kSelectChunk)),
+        n(min(p.N - base, p.per * unsigned(kSelectChunk))),
+        nc((n + unsigned(kSelectChunk) - 1u) / unsigned(kSelectChunk)),
+        hg(11u * g) {}
+  __device__ unsigned piece(unsigned i, unsigned j) const {  // j < nc
+    const unsigned q = i >> 2, rev = ((q & 1u) << 4) | ((q & 2u) << 2) | (q & 4u);
+    const unsigned x = ((((rev + hg) & 31u) * nc) >> 5) + j;
+    return x >= nc ? x - nc : x;
+  }
+  // offset in the range of slot i of round j for this lane, less lane_offset()
+  __device__ unsigned slot_offset(unsigned i, unsigned j) const {
+    return (unsigned(kThreads) * i) * nc + 64u * piece(i, j);
+  }
+  __device__ unsigned lane_offset() const { return (threadIdx.x & ~63u) * nc + lane_id(); }
+  // Valid slots of round j (only the last range of a request is ragged).
+  __device__ unsigned valid(unsigned j) const {
+    if (j >= nc) return 0u;
+    if (n == nc * unsigned(kSelectChunk)) return ~0u;
+    const unsigned lo = lane_offset();
+    unsigned vm = 0u;
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) vm |= unsigned(lo + slot_offset(unsigned(i), j) < n) << i;
+    return vm;
+  }
+};
+
+// The log-probabilities of a round on their way: the beam scores are added when they
 // have come.
 struct RawScores {
   float x[kNI];
   unsigned vm;
 };
-template <bool BEAM>
-__device__ inline void issue_scores(const SelectParams& p, unsigned r, unsigned base, unsigned n,
-                                    RawScores& l) {
-  l.vm = valid_mask(n);
-  const float* logp_r = p.logp + size_t(r) * p.N;
+// Round j (past the last one: the last again, none valid).
+__device__ inline void issue_scores(const SelectParams& p, unsigned r, const StreamRange& s,
+                                    unsigned j, RawScores& l) {
+  l.vm = s.valid(j);
+  j = min(j, s.nc - 1u);
+  // (slots past the range's end touch no memory)
+  const __amdgpu_buffer_rsrc_t rs =
+      buffer_rsrc(p.logp + size_t(r) * p.N + s.base, int(s.n * 4u));
+  const unsigned lo = s.lane_offset();
 #pragma unroll
-  for (int i = 0; i < kNI; ++i)
-    l.x[i] = logp_r[((l.vm >> i) & 1u) ? base + threadIdx.x + unsigned(i) * kThreads : base];
+  for (int i = 0; i < kNI; ++i) {
+    unsigned so = s.slot_offset(unsigned(i), j);
+    // (a scalar added at the load: left alone, 32 lane offsets stay in registers
+    // from round to round)
+    asm volatile("" : "+s"(so));
+    l.x[i] = __uint_as_float(
+        unsigned(__builtin_amdgcn_raw_buffer_load_b32(rs, int(4u * (lo + so)), 0, 0)));
+  }
 }
 
-// Candidate scores of the loaded chunk; invalid slots are NaN, which no bound keeps.
-// Where each wave's slot lies in one row and a chunk in at most 34 rows, the beam
-// scores are one load (lane l: row row0 + l) and a lane read per slot; otherwise a
-// load per slot.  The streaming form works on scores and forms keys only for
-// the lanes' maxima and the survivors: at four chunks per compute unit the keys' ten
-// vector instructions per candidate cost more than the reads (a plain read of 67 MB
-// takes 10.5 us here).
+// The beam scores of a range, from its first row on: lane l holds row row0 + l.
+struct BeamRows {
+  unsigned row0, rem0;  // the range's first row, and its start in that row
+  unsigned dr, dm;      // a step of one slot, in rows and remainder
+  bool lanes;           // every piece lies in one row, at most 64 rows
+  float bv;
+  template <bool BEAM>
+  __device__ void init(const SelectParams& p, unsigned r, const StreamRange& s) {
+    if constexpr (BEAM) {
+      row0 = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(s.base, p.V, p.inv_v))));
+      rem0 = s.base - row0 * p.V;
+      const unsigned step = unsigned(kThreads) * s.nc;
+      dr = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(step, p.V, p.inv_v))));
+      dm = step - dr * p.V;
+      lanes = (p.V & 63u) == 0u && s.n <= 62u * p.V;
+      bv = p.beam[size_t(r) * p.W_prev + min(row0 + lane_id(), p.W_prev - 1u)];
+    }
+  }
+};
+
+// Candidate scores of the loaded round j; invalid slots are NaN, which no bound keeps.
+// Where each piece lies in one row and the range in at most 64 rows, the beam scores
+// are one load per range and a lane read per slot; otherwise a load per slot.  The
+// streaming form works on scores and forms keys only for the lanes' maxima and the
+// survivors: at four rounds the keys' ten vector instructions per candidate cost
+// more than the reads (a plain read of 67 MB takes 10.5 us here).
 template <bool BEAM>
-__device__ inline void score_vals(const SelectParams& p, unsigned r, unsigned base,
-                                  const RawScores& l, float (&v)[kNI]) {
+__device__ inline void score_vals(const SelectParams& p, unsigned r, const StreamRange& s,
+                                  const BeamRows& b, unsigned j, const RawScores& l,
+                                  float (&v)[kNI]) {
   const float nan = __uint_as_float(0x7fc00000u);
   if constexpr (!BEAM) {
 #pragma unroll
     for (int i = 0; i < kNI; ++i) v[i] = l.x[i];
   } else {
-    const float* beam_r = p.beam + size_t(r) * p.W_prev;
-    if (p.V >= unsigned(kThreads) && (p.V & 63u) == 0u) {
-      const unsigned row0 = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(base, p.V, p.inv_v))));
-      const float bv = beam_r[min(row0 + lane_id(), p.W_prev - 1u)];
-      unsigned rel = 0u;  // of the wave's slot: its row, from row0, and its offset there
-      unsigned rem = base + unsigned(__builtin_amdgcn_readfirstlane(int(threadIdx.x & ~63u))) - row0 * p.V;
-      if (rem >= p.V) {
-        rem -= p.V;
-        ++rel;
-      }
+    j = min(j, s.nc - 1u);
+    if (b.lanes) {
+      const unsigned w0 = b.rem0 + unsigned(__builtin_amdgcn_readfirstlane(int(threadIdx.x & ~63u))) * s.nc;
 #pragma unroll
-      for (int i = 0; i < kNI; ++i) {
-        v[i] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bv), rel)) + l.x[i];
-        rem += kThreads;
-        if (rem >= p.V) {
-          rem -= p.V;
-          ++rel;
+      for (int q = 0; q < kNI / 4; ++q) {  // (turn() holds for four slots)
+        const unsigned x = w0 + s.slot_offset(4u * unsigned(q), j);
+        unsigned rel = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(x, p.V, p.inv_v))));
+        unsigned rem = x - rel * p.V;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[4 * q + e] =
+              __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(b.bv), rel)) + l.x[4 * q + e];
+          rel += b.dr;
+          rem += b.dm;
+          if (rem >= p.V) {
+            rem -= p.V;
+            ++rel;
+          }
         }
       }
     } else {
+      const __amdgpu_buffer_rsrc_t rs =
+          buffer_rsrc(p.beam + size_t(r) * p.W_prev + b.row0, int((p.W_prev - b.row0) * 4u));
       float bs[kNI];
 #pragma unroll
-      for (int i = 0; i < kNI; ++i) {
-        const unsigned pos = base + threadIdx.x + unsigned(i) * kThreads;
-        bs[i] = beam_r[((l.vm >> i) & 1u) ? row_of(pos, p.V, p.inv_v) : 0u];
+      for (int q = 0; q < kNI / 4; ++q) {
+        const unsigned x = b.rem0 + s.lane_offset() + s.slot_offset(4u * unsigned(q), j);
+        unsigned rel = row_of(x, p.V, p.inv_v), rem = x - rel * p.V;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          bs[4 * q + e] = __uint_as_float(
+              unsigned(__builtin_amdgcn_raw_buffer_load_b32(rs, int(4u * rel), 0, 0)));
+          rel += b.dr;
+          rem += b.dm;
+          if (rem >= p.V) {
+            rem -= p.V;
+            ++rel;
+          }
+        }
       }
 #pragma unroll
       for (int i = 0; i < kNI; ++i) v[i] = bs[i] + l.x[i];
     }
   }
-  if (__ballot(l.vm != ~0u) != 0ull) {  // (a whole chunk has no invalid slot)
+  if (__ballot(l.vm != ~0u) != 0ull) {  // (a whole round has no invalid slot)
 #pragma unroll
     for (int i = 0; i < kNI; ++i) v[i] = ((l.vm >> i) & 1u) ? v[i] : nan;
   }
@@ -2113,34 +2243,23 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p)
   const unsigned r = blockIdx.x / p.groups, g = blockIdx.x - r * p.groups;
   const unsigned t = threadIdx.x, lane = lane_id(), w = t >> 6;
   const unsigned tag = p.ctl->epoch + 1u;  // (the final kernel advances the epoch)
-  // chunks c0 .. c0 + nc - 1 (at least one), read from the last on where `back`
-  auto backwards = [&](unsigned i) { return (i & 1u) != 0u || (i != 0u && i == p.groups - 1u); };
-  auto sampled = [&](unsigned i) {
-    return backwards(i) ? min((i + 1u) * p.per, p.nwg) - 1u : i * p.per;
-  };
-  const unsigned c0 = g * p.per, nc = min(p.per, p.nwg - c0), first = sampled(g);
-  const bool back = backwards(g);
+  const StreamRange rg(p, g);
+  const unsigned c0 = g * p.per;  // round j fills the slot of chunk c0 + j
   const unsigned nseg = p.groups * unsigned(SPC);
-  auto chunk_at = [&](unsigned j) __attribute__((always_inline)) {  // the j-th read (clamped)
-    const unsigned i = min(j, nc - 1u);
-    return back ? first - i : first + i;
-  };
-  auto base_of = [&](unsigned j) __attribute__((always_inline)) {
-    return chunk_at(j) * unsigned(kSelectChunk);
-  };
-  auto issue = [&](unsigned j, RawScores& l) __attribute__((always_inline)) {  // (past the last: none valid)
-    const unsigned base = base_of(j);
+  auto issue = [&](unsigned j, RawScores& l) __attribute__((always_inline)) {
     __builtin_amdgcn_sched_barrier(0);
-    issue_scores<BEAM>(p, r, base, j < nc ? min(p.N - base, unsigned(kSelectChunk)) : 0u, l);
+    issue_scores(p, r, rg, j, l);
     __builtin_amdgcn_sched_barrier(0);
   };
-  float val[kNI], val1[kNI];  // the chunks read as 0, 2, ... and as 1, 3, ...
+  BeamRows br;
+  br.init<BEAM>(p, r, rg);
+  float val[kNI], val1[kNI];  // the rounds 0, 2, ... and 1, 3, ...
   RawScores la, lb;
   issue(0u, la);
-  score_vals<BEAM>(p, r, base_of(0u), la, val);
-  const unsigned vm = la.vm;
+  score_vals<BEAM>(p, r, rg, br, 0u, la, val);
+  unsigned vm = la.vm;
   issue(1u, lb);
-  {  // the first chunk's summaries (the largest of a lane's numbers; key 0 if it has none)
+  {  // the sample's summaries (the largest of a lane's numbers; key 0 if it has none)
     const unsigned lmax = order_key(lane_best(val));
     const bool live = vm & 1u;
     if constexpr (SPC == kWaves) {
@@ -2171,73 +2290,66 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p)
   if (g == 0u) {
     uint4 e[kOnePassSegPer];
     const int late = onepass_poll(p, r, tag, e, nseg);
-    bw = onepass_bound<kOnePassSegPer, SPC>(p, sh, bs, e, late, word, nseg, sampled);
-    score_vals<BEAM>(p, r, base_of(1u), lb, val1);
+    const unsigned per = p.per;
+    // (c* is the first chunk of a range)
+    bw = onepass_bound<kOnePassSegPer, SPC>(p, sh, bs, e, late, word, nseg,
+                                            [per](unsigned i) { return i * per; });
+    score_vals<BEAM>(p, r, rg, br, 1u, lb, val1);
     issue(2u, la);
   } else {
-    // (the second chunk's scores are formed while the bound is, and the third's
-    // loads issued; B and c*: c* comes about 1 us after B, and chunks after the
+    // (the second round's scores are formed while the bound is, and the third's
+    // loads issued; B and c*: c* comes about 1 us after B, and ranges after the
     // first need it)
-    score_vals<BEAM>(p, r, base_of(1u), lb, val1);
+    score_vals<BEAM>(p, r, rg, br, 1u, lb, val1);
     issue(2u, la);
     if (t == 0) bw_sh[0] = wait_bound(word, p.wait_ticks, true);
     __syncthreads();
     bw = bw_sh[0];  // 0 after a timeout: no bound
   }
   const unsigned B = unsigned(bw), cstar = unsigned(bw >> 32) - 1u;
-  auto bound_of = [&](unsigned c) { return (c > cstar && B < ~0u) ? B + 1u : B; };
-  unsigned long long over = 0ull;  // reads whose survivors overflow their slot
-  // (inlined by force: called, the lambdas' captures, the keys among them, would
+  // (every candidate of the ranges after c*'s follows every one of its own)
+  unsigned bound = (c0 > cstar && B < ~0u) ? B + 1u : B;
+  // (inlined by force: called, the lambda's captures, the scores among them, would
   // live in scratch)
   auto filter = [&](unsigned j, unsigned vmask, const float(&v)[kNI]) __attribute__((always_inline)) {
-    const unsigned c = chunk_at(j), bound = bound_of(c), base = c * unsigned(kSelectChunk);
-    const unsigned keep = kept_mask(v, vmask, bound);
-    const unsigned total = replan_sparse(keep, sh);
-    if (total > p.cap) {  // rare: cut below, from a second read
-      over |= 1ull << j;
-    } else {
-      uint2* out = p.cand_out + (size_t(r) * p.nwg + c) * p.cap;
-      ordered_apply_sparse(keep, sh, [&](int i, unsigned rank) __attribute__((always_inline)) {
-        out[rank] = make_uint2(order_key(v[i]), base + unsigned(i) * kThreads + t);
-      });
-      if (t == 0)  // (the placing kernel does not read a largest key)
-        reinterpret_cast<uint2*>(p.cnt_out)[size_t(r) * p.nwg + c] = make_uint2(total, 0u);
+    unsigned keep = kept_mask(v, vmask, bound);
+    unsigned total = replan_sparse(keep, sh);
+    if (__builtin_expect(total > p.cap, 0)) {
+      // at least the round's top W, as many as the slot takes; the last key bounds
+      // the rounds after it too, so that a range that holds most of the best scores, or
+      // a workgroup without a bound, takes this once and not in every round
+      __syncthreads();
+      // (formed at each use: kept, the keys would take 32 more registers)
+      auto key = [&](int i) __attribute__((always_inline)) {
+        float x = v[i];
+        asm volatile("" : "+v"(x));
+        return order_key(x);
+      };
+      const Cut cut = find_cut_of<false>(sh, key, keep, p.W, p.cap);
+      keep = cut_mask_of(sh, key, keep, cut);
+      bound = max(bound, cut.tau);
+      total = replan_sparse(keep, sh);
     }
+    uint2* out = p.cand_out + (size_t(r) * p.nwg + c0 + j) * p.cap;
+    const unsigned lo = rg.base + rg.lane_offset();
+    ordered_apply_sparse(keep, sh, [&](int i, unsigned rank) __attribute__((always_inline)) {
+      out[rank] = make_uint2(order_key(v[i]), lo + rg.slot_offset(unsigned(i), j));
+    });
+    if (t == 0)  // (the placing kernel does not read a largest key)
+      reinterpret_cast<uint2*>(p.cnt_out)[size_t(r) * p.nwg + c0 + j] = make_uint2(total, 0u);
     __syncthreads();  // every wave has read sh.tab
   };
-  filter(0u, vm, val);
-  for (unsigned j = 1u; j < nc; j += 2u) {
+  for (unsigned j = 0u;; j += 2u) {
+    filter(j, vm, val);
+    if (j + 1u == rg.nc) break;
+    if (j != 0u) score_vals<BEAM>(p, r, rg, br, j + 1u, lb, val1);
     const unsigned vm1 = lb.vm;
-    issue(j + 2u, lb);
-    filter(j, vm1, val1);
-    if (j + 1u == nc) break;
-    score_vals<BEAM>(p, r, base_of(j + 1u), la, val);
-    const unsigned vm0 = la.vm;
-    issue(j + 3u, la);
-    filter(j + 1u, vm0, val);
-    if (j + 2u < nc) score_vals<BEAM>(p, r, base_of(j + 2u), lb, val1);
-  }
-  for (; over != 0ull; over &= over - 1ull) {  // a chunk's exact top W of its survivors
-    const unsigned c = chunk_at(unsigned(__builtin_ctzll(over))), bound = bound_of(c);
-    const unsigned base = c * unsigned(kSelectChunk);
-    // (the mask that overflowed, as the cut needs at least W: a bound of +0 keeps the -0s
-    // as scores, and compared as keys fewer than W may be left)
-    unsigned key[kNI];
-    const unsigned vmask =
-        load_scores<BEAM>(p, r, base, min(p.N - base, unsigned(kSelectChunk)), val);
-    unsigned keep = kept_mask(val, vmask, bound);
-#pragma unroll
-    for (int i = 0; i < kNI; ++i) key[i] = order_key(val[i]);
-    __syncthreads();
-    keep = cut_mask(sh, key, keep, find_cut(sh, key, keep, p.W));
-    const unsigned total = replan_sparse(keep, sh);
-    uint2* out = p.cand_out + (size_t(r) * p.nwg + c) * p.cap;
-    ordered_apply_sparse(keep, sh, [&](int i, unsigned rank) __attribute__((always_inline)) {
-      out[rank] = make_uint2(key[i], base + unsigned(i) * kThreads + t);
-    });
-    if (t == 0)
-      reinterpret_cast<uint2*>(p.cnt_out)[size_t(r) * p.nwg + c] = make_uint2(total, 0u);
-    __syncthreads();
+    issue(j + 3u, lb);
+    filter(j + 1u, vm1, val1);
+    if (j + 2u == rg.nc) break;
+    score_vals<BEAM>(p, r, rg, br, j + 2u, la, val);
+    vm = la.vm;
+    issue(j + 4u, la);
   }
 }
 

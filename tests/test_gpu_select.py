@@ -59,11 +59,13 @@ CASES = [
     ("two_pass_summary_rising_r8", 8, 256, SELECT_CODEBOOK, 256, "rising", True),
     ("two_pass_summary_r4_w1024_ties", 4, 1024, 4096, 1024, "ties", True),
     ("two_pass_summary_rows8", 2, 1024, SELECT_CODEBOOK, 256, "logsoftmax", True),
-    # streaming form (more chunks than fit at once; two to four per workgroup):
-    # rows that straddle a wave's slot and a ragged last chunk with special
+    # streaming form (more chunks than fit at once; two rounds per workgroup):
+    # rows that straddle a wave's piece and a ragged last chunk with special
     # values, rows shorter than a workgroup, no beam scores, a row per 16
     # lanes' and per wave's summaries, slots that overflow, W = 1, one
-    # workgroup with fewer chunks than the others
+    # workgroup with fewer chunks than the others; then a last range of one
+    # candidate and of one more than a chunk, 57 short rows in a range with pieces of
+    # one row each, and 4, 7 and 13 rounds (13: odd rows with special values)
     ("stream_special_ragged", 3, 500, 3001, 200, "special", True),
     ("stream_short_rows", 3, 5000, 300, 128, "logsoftmax", True),
     ("stream_no_beam", 5, 108, SELECT_CODEBOOK, 150, "special", False),
@@ -71,6 +73,13 @@ CASES = [
     ("stream_rising_overflow", 4, 133, SELECT_CODEBOOK, 40, "rising", True),
     ("stream_ties_overflow", 4, 131, SELECT_CODEBOOK, 33, "ties", True),
     ("stream_width_one", 9, 60, SELECT_CODEBOOK, 1, "logsoftmax", True),
+    ("stream_last_one", 4, 1, 68 * 16384 + 1, 20, "special", True),
+    ("stream_last_chunk_and_one", 4, 1, 69 * 16384 + 1, 20, "ties", True),
+    ("stream_rows_of_576", 4, 2000, 576, 60, "logsoftmax", True),
+    ("stream_4_rounds", 8, 250, SELECT_CODEBOOK, 256, "logsoftmax", True),
+    ("stream_4_rounds_ties", 4, 64, 65536, 64, "ties", True),
+    ("stream_7_rounds_rising", 60, 50, 8000, 16, "rising", True),
+    ("stream_13_rounds_special", 50, 101, 9973, 11, "special", True),
 ]
 
 
@@ -152,6 +161,64 @@ def test_select_signed_zeros_at_the_bound(R, P, V, W, at):
     logp = logp.reshape(R, P, V)
     print(f"signed zeros R={R} W_prev={P} V={V} W={W} {at}", flush=True)
     par, tok, sc = BeamSelector(R, P, V, W)(torch.from_numpy(logp).cuda(), None)
+    torch.cuda.synchronize()
+    _check(logp, None, W, par.cpu().numpy(), tok.cpu().numpy(), sc.cpu().numpy())
+
+
+def _counts(sel):
+    """The survivors that each chunk's slot (one-pass, streaming and two-pass
+    forms) holds after a call, [R][nchunks], read from the workspace."""
+    n = sel.prev_width * sel.vocab
+    nchunks = -(-n // 16384)
+    cap = max(64, 1 << (2 * sel.width - 1).bit_length())
+    if cap > 4096:
+        cap = max(4096, 1 << (sel.width - 1).bit_length())
+    up = lambda x: -(-x // 256) * 256
+    off = 1024 + 8192 * 16 + up(sel.R * nchunks * 8 * 16) + up(sel.R * 8) \
+        + up(sel.R * nchunks * cap * 8)
+    raw = sel.workspace[off:off + sel.R * nchunks * 8].cpu().numpy().view(np.uint32)
+    return raw.reshape(sel.R, nchunks, 2)[:, :, 0]
+
+
+@pytest.mark.parametrize("R,P,V,W", [(4, 64, 65536, 64), (16, 16, 131072, 16)])
+def test_select_streaming_samples_every_part_of_the_rows(R, P, V, W):
+    """The streaming form takes its bound from the first round of each
+    workgroup's reads.  With the better tokens in the middle half of a
+    vocabulary that is as long as a workgroup's range, whole chunks as rounds would
+    sample the outer quarters only, and nearly all slots would overflow and
+    be cut to W; a sample of all parts leaves a few times W survivors (expected
+    about 5 W, 16 W allowed)."""
+    import torch
+    from paper_2609_12399_amd.runner import BeamSelector
+    rng = np.random.default_rng(3)
+    logp = (rng.standard_normal((R, P, V), dtype=np.float32) * 2).astype(np.float32)
+    logp[:, :, V // 4:3 * V // 4] += 8.0
+    beam = np.zeros((R, P), dtype=np.float32)
+    print(f"sampled parts R={R} W_prev={P} V={V} W={W}", flush=True)
+    sel = BeamSelector(R, P, V, W)
+    par, tok, sc = sel(torch.from_numpy(logp).cuda(), torch.from_numpy(beam).cuda())
+    torch.cuda.synchronize()
+    _check(logp, beam, W, par.cpu().numpy(), tok.cpu().numpy(), sc.cpu().numpy())
+    kept = _counts(sel).sum(axis=1)
+    assert (kept >= W).all() and (kept <= 16 * W).all(), kept
+
+
+@pytest.mark.parametrize("W", [40, 256])
+def test_select_streaming_many_ties_beyond_the_staged_ones(W):
+    """More tied survivors than the placing kernel stages, in slots that are not
+    in index order (a range's rounds interleave): the lowest flat indices are
+    kept."""
+    import torch
+    from paper_2609_12399_amd.runner import BeamSelector
+    R, P, V = 8, 256, SELECT_CODEBOOK
+    rng = np.random.default_rng(5)
+    logp = (-1.0 - rng.random((R, P * V), dtype=np.float32)).astype(np.float32)
+    logp[:, rng.permutation(P * V)[:P * V // 3]] = 0.5
+    logp[0, rng.permutation(P * V)[:W // 2]] = 1.0
+    logp = logp.reshape(R, P, V)
+    print(f"tied survivors, streaming W={W}", flush=True)
+    sel = BeamSelector(R, P, V, W)
+    par, tok, sc = sel(torch.from_numpy(logp).cuda(), None)
     torch.cuda.synchronize()
     _check(logp, None, W, par.cpu().numpy(), tok.cpu().numpy(), sc.cpu().numpy())
 
