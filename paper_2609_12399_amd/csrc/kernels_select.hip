@@ -88,7 +88,7 @@ struct SelectParams {
   // one-pass path
   struct OnePassCtl* ctl;   // call counter and per-request bound words
   uint4* ex;                // [R][nseg] per wave: (M, m, kM, check), see the one-pass path
-  unsigned long long wait_ticks;  // how long a workgroup waits for the bound (wall clock)
+  unsigned long long wait_ticks;  // how long a request waits for its summaries (wall clock)
   unsigned fparts;          // workgroups per request of the final kernel
   // two-pass path with a bound word per request (see select_summary_kernel)
   unsigned long long* tp_bound;  // [R] (c* + 1) << 32 | B, or null: the filter forms the bound
@@ -100,8 +100,9 @@ struct SelectParams {
 // starts, and the call's final kernel zeroes its requests' words again; the
 // epoch counts the calls (see the summaries' tags).
 struct OnePassCtl {
-  unsigned epoch;     // this call's tag is epoch + 1
-  unsigned pad_[3];
+  unsigned epoch;       // this call's tag is epoch + 1
+  unsigned wait_shift;  // the waits are wait_ticks >> wait_shift (0; a test plants more)
+  unsigned pad_[2];
   unsigned long long bound[kSelectOnePassMaxRequests];  // (1 << 32) | bound, once known
   // two-pass summary pass: workgroups of each request that have published
   // their summaries (zero between calls: the last one returns it to zero)
@@ -454,17 +455,14 @@ struct Cut {
 // keys.  Radix passes of up to 11 bits run over key - lo (lo: the smallest
 // valid key), from its top bit down, and stop early when the boundary bin is
 // taken whole.
-// key(i): the key of slot i.  Unless EXACT any cut that keeps need to most keys will do
-// (usually the first pass finds one).
-template <bool EXACT, typename KeyOf>
-__device__ inline Cut find_cut_of(SelShared& sh, KeyOf&& key, unsigned vm, unsigned need,
-                                  unsigned most) {
+__device__ inline Cut find_cut(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
+                               unsigned need) {
   unsigned lo = ~0u, hi = 0u;
 #pragma unroll
   for (int i = 0; i < kNI; ++i)
     if ((vm >> i) & 1u) {
-      lo = min(lo, key(i));
-      hi = max(hi, key(i));
+      lo = min(lo, key[i]);
+      hi = max(hi, key[i]);
     }
   const Red3 r = block_reduce(sh, 0u, lo, hi);
   if (r.lo == r.hi) return Cut{r.lo, need, ~0u};  // all equal: ties by position
@@ -479,34 +477,28 @@ __device__ inline Cut find_cut_of(SelShared& sh, KeyOf&& key, unsigned vm, unsig
     const unsigned mask = (1u << bits) - 1u;
 #pragma unroll
     for (int i = 0; i < kNI; ++i) {
-      const unsigned rel = key(i) - r.lo;
+      const unsigned rel = key[i] - r.lo;
       const bool act = ((vm >> i) & 1u) && shr(rel, shift + bits) == prefix;
       hist_add(sh.hist, (rel >> shift) & mask, act);
     }
     __syncthreads();
     find_bin(sh, need);
     prefix = (prefix << bits) | sh.digit;
-    if constexpr (!EXACT) most -= need - sh.need;  // (less the keys above the bin)
     need = sh.need;
     const unsigned cnt = sh.cnt;
-    if (EXACT ? cnt == need : cnt <= most) return Cut{r.lo + (prefix << shift), 0u, 0u};
+    if (cnt == need) return Cut{r.lo + (prefix << shift), 0u, 0u};
     if (shift == 0) return Cut{r.lo + prefix, need, cnt};
   }
 }
 
-__device__ inline Cut find_cut(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
-                               unsigned need) {
-  return find_cut_of<true>(sh, [&](int i) { return key[i]; }, vm, need, need);
-}
-
 // Selection mask of a cut (bit i: slot i); ties resolved in position order.
-template <typename KeyOf>
-__device__ inline unsigned cut_mask_of(SelShared& sh, KeyOf&& key, unsigned vm, const Cut& c) {
+__device__ inline unsigned cut_mask(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
+                                    const Cut& c) {
   unsigned ge = 0u, eq = 0u;
 #pragma unroll
   for (int i = 0; i < kNI; ++i) {
-    ge |= unsigned(c.take == 0u ? key(i) >= c.tau : key(i) > c.tau) << i;
-    eq |= unsigned(key(i) == c.tau) << i;
+    ge |= unsigned(c.take == 0u ? key[i] >= c.tau : key[i] > c.tau) << i;
+    eq |= unsigned(key[i] == c.tau) << i;
   }
   ge &= vm;
   if (c.take == 0u) return ge;
@@ -520,11 +512,6 @@ __device__ inline unsigned cut_mask_of(SelShared& sh, KeyOf&& key, unsigned vm, 
     eq &= ~drop;
   }
   return ge | eq;
-}
-
-__device__ inline unsigned cut_mask(SelShared& sh, const unsigned (&key)[kNI], unsigned vm,
-                                    const Cut& c) {
-  return cut_mask_of(sh, [&](int i) { return key[i]; }, vm, c);
 }
 
 // ---- loads -----------------------------------------------------------------
@@ -1283,8 +1270,9 @@ __global__ __launch_bounds__(kThreads) void select_rank_kernel(SelectParams p) {
 //      (equal or higher keys at lower indices), so it cannot be kept (this
 //      keeps tied scores from surviving in every chunk).  B is published
 //      before c*, for which only chunks holding a key equal to B wait.  The
-//      others wait for the bound word for a bounded time; one that gives up
-//      keeps its chunk's exact top W instead (slower, never wrong);
+//      waits are bounded: past its own the first workgroup takes the bound
+//      from the summaries that have come, and a workgroup that gives up on the
+//      bound word takes its own from them (a looser bound: slower, never wrong);
 //   3. every workgroup keeps its candidates above B, or equal to B in a
 //      chunk up to c*, in its chunk's slot, in index order (the chunk's
 //      exact top W when they overflow it), with the count and the chunk's
@@ -1302,16 +1290,20 @@ __global__ __launch_bounds__(kThreads) void select_rank_kernel(SelectParams p) {
 // guarantee only one candidate per wave.
 
 // The bound word of a request: (h << 32) | B.  h = 0: nothing yet; h =
-// kCstarPending: B is known and c* is not; otherwise h = c* + 1.  A call
-// that gave up on the summaries publishes B = 0 with h = kNoBound (no chunk
-// above c*, so nothing is dropped).
+// kCstarPending: B is known and c* is not; otherwise h = c* + 1.
 constexpr unsigned kCstarPending = ~0u;
-constexpr unsigned kNoBound = ~0u - 1u;
+
+// How long the request's first workgroup waits for the summaries.
+__device__ inline unsigned long long summary_ticks(const SelectParams& p) {
+  return p.wait_ticks >> (p.ctl->wait_shift & 63u);
+}
 
 // Waits (thread 0) for the bound word of a request, for B alone or (final)
-// also for c*; 0 after `ticks`.
-__device__ inline unsigned long long wait_bound(unsigned long long* word,
-                                                unsigned long long ticks, bool final) {
+// also for c*; 0 after twice the wait for the summaries (at whose end the first
+// workgroup forms the bound from those that have come).
+__device__ inline unsigned long long wait_bound(const SelectParams& p, unsigned long long* word,
+                                                bool final) {
+  const unsigned long long ticks = 2ull * summary_ticks(p);
   const unsigned long long t0 = static_cast<unsigned long long>(wall_clock64());
   for (;;) {
     const unsigned long long v = __hip_atomic_load(word, __ATOMIC_RELAXED,
@@ -1342,6 +1334,7 @@ __device__ inline uint4 ld_agent4(__amdgpu_buffer_rsrc_t rs, unsigned off) {
 // covers stores on this architecture), before a counter tells others that
 // they are there.
 __device__ inline void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
+__device__ inline void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // Tags of the one-pass wave summaries.  A summary (M, m, kM) is stored as one
 // 16-byte word whose last field is tag ^ mix(M, m, kM), tag = epoch + 1 of the
@@ -1373,16 +1366,18 @@ struct BoundShared {
   uint2 ev[kBoundList];          // (key, weight) of the events in the chosen bin
   unsigned nev;
   unsigned red[2][kWaves];
-  unsigned late[kWaves];         // threads of each wave whose poll gave up
   alignas(16) unsigned gc[kOnePassSegPer * kThreads / kWaves];  // guaranteed count at B per chunk
 };
 
 // Reads request r's wave summaries until every one of this thread's carries
 // `tag` (thread t: summaries i * kThreads + t, all rows loaded in each round,
-// the ones beyond nseg outside the buffer, reading zeros); 1 when the waiting
-// time passed first.  No barrier: onepass_bound's first one joins the threads.
-__device__ inline int onepass_poll(const SelectParams& p, unsigned r, unsigned tag,
-                                   uint4 (&e)[kOnePassSegPer], unsigned nseg) {
+// the ones beyond nseg outside the buffer, reading zeros), or `ticks` have
+// passed: the missing ones are then zero, which says of their lanes only that
+// they hold a candidate each (kernels beside this one can keep workgroups off
+// the chip or their loads back).  No barrier: onepass_bound's first one joins the threads.
+__device__ inline void onepass_poll(const SelectParams& p, unsigned r, unsigned tag,
+                                    uint4 (&e)[kOnePassSegPer], unsigned nseg,
+                                    unsigned long long ticks) {
   const unsigned t = threadIdx.x;
   const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(p.ex + size_t(r) * nseg, int(nseg * 16u));
   unsigned pending = 0u;
@@ -1390,26 +1385,26 @@ __device__ inline int onepass_poll(const SelectParams& p, unsigned r, unsigned t
   for (int i = 0; i < kOnePassSegPer; ++i)
     pending |= unsigned(unsigned(i) * kThreads + t < nseg) << i;
   const unsigned long long t0 = static_cast<unsigned long long>(wall_clock64());
-  int late = 0;
   while (pending != 0u) {
 #pragma unroll
     for (int i = 0; i < kOnePassSegPer; ++i) e[i] = ld_agent4(rs, (unsigned(i) * kThreads + t) * 16u);
 #pragma unroll
     for (int i = 0; i < kOnePassSegPer; ++i)
       if (summary_tag(e[i]) == tag) pending &= ~(1u << i);
-    if (static_cast<unsigned long long>(wall_clock64()) - t0 > p.wait_ticks) {
-      late = 1;
-      break;
-    }
+    if (static_cast<unsigned long long>(wall_clock64()) - t0 > ticks) break;
   }
-  return late;
+  if (pending != 0u) {
+#pragma unroll
+    for (int i = 0; i < kOnePassSegPer; ++i)
+      if ((pending >> i) & 1u) e[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
 }
 
 // Bound word of request r from every wave's summary (see step 2 above):
-// ((c* + 1) << 32) | B, also published to `word` (thread 0): first with B
+// ((c* + 1) << 32) | B, also published to `word` (thread 0; unless null): first with B
 // alone, then with c*.  Thread t holds summaries i * kThreads + t in e[i]
-// (nseg <= kOnePassSegPer * kThreads) from onepass_poll, which gave up when
-// `late` is set in any thread: then the word says no bound (B = 0).
+// (nseg <= kOnePassSegPer * kThreads) from onepass_poll (one that did not come in time:
+// zero).
 //
 // Each live summary (M, m, kM) of a wave with nl live lanes is two weighted
 // events: (M, kM) and (m, nl - kM).  The guaranteed count at a key x is the
@@ -1430,8 +1425,7 @@ struct EveryChunk {
 template <int ROWS = kOnePassSegPer, int SPC = kWaves, typename ChunkOf = EveryChunk>
 __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelShared& sh,
                                                    BoundShared& bs, const uint4 (&e)[ROWS],
-                                                   int late, unsigned long long* word,
-                                                   unsigned nseg, ChunkOf chunk_of = {}) {
+                                                   unsigned long long* word, unsigned nseg, ChunkOf chunk_of = {}) {
   const unsigned t = threadIdx.x, lane = lane_id(), w = t >> 6;
   const unsigned W = p.W;
   reinterpret_cast<uint4*>(sh.hist)[t] = make_uint4(0u, 0u, 0u, 0u);
@@ -1449,28 +1443,20 @@ __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelSha
       }
     }
   }
-  {  // (with the poll's wait flags: one barrier for both)
-    const Red3 wr = wave_reduce(unsigned(late), lo, hi);
+  {
+    const Red3 wr = wave_reduce(0u, lo, hi);
     if (lane == 0) {
       bs.red[0][w] = wr.lo;
       bs.red[1][w] = wr.hi;
-      bs.late[w] = wr.sum;
     }
   }
   __syncthreads();
   lo = ~0u;
   hi = 0u;
-  unsigned nlate = 0u;
 #pragma unroll
   for (int w2 = 0; w2 < kWaves; ++w2) {
     lo = min(lo, bs.red[0][w2]);
     hi = max(hi, bs.red[1][w2]);
-    nlate += bs.late[w2];
-  }
-  if (nlate != 0u) {
-    const unsigned long long none = static_cast<unsigned long long>(kNoBound) << 32;
-    if (t == 0) __hip_atomic_store(word, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return none;
   }
   unsigned B = lo;
   if (lo < hi) {
@@ -1556,7 +1542,7 @@ __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelSha
     }
   }
   // B alone first: only chunks holding a key equal to B wait for c*
-  if (t == 0)
+  if (t == 0 && word != nullptr)
     __hip_atomic_store(word, (static_cast<unsigned long long>(kCstarPending) << 32) | B,
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // c*: the chunks' guaranteed counts at B, summed in chunk order.  Thread t
@@ -1596,7 +1582,8 @@ __device__ inline unsigned long long onepass_bound(const SelectParams& p, SelSha
   __syncthreads();
   const unsigned long long bw =
       (static_cast<unsigned long long>(chunk_of(sh.digit) + 1u) << 32) | B;
-  if (t == 0) __hip_atomic_store(word, bw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (t == 0 && word != nullptr)
+    __hip_atomic_store(word, bw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return bw;
 }
 
@@ -2009,35 +1996,36 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
   }
   // 2. the bound: computed by the request's first workgroup once every
   // summary is in, waited for by the others
-  unsigned bound;  // keys below it are dropped
   unsigned long long* const word = &p.ctl->bound[r];
-  if (c == 0u) {  // (chunk 0 is never above c*: its bound is B)
-    uint4 e[kOnePassSegPer];
-    const int late = onepass_poll(p, r, tag, e, p.nseg);
-    bound = unsigned(onepass_bound(p, sh, bs, e, late, word, p.nseg));
-  } else {
-    if (t == 0) bw_sh[0] = wait_bound(word, p.wait_ticks, false);
+  unsigned long long bw = 0ull;
+  if (c != 0u) {
+    if (t == 0) bw_sh[0] = wait_bound(p, word, false);
     __syncthreads();
-    unsigned long long bw = bw_sh[0];  // 0 after a timeout: no bound
-    if (unsigned(bw >> 32) == kCstarPending) {
-      // c* decides only for keys equal to B: a chunk holding none keeps the
-      // keys >= B whichever side of c* it is on
-      // (compared as scores: the other zero counts as equal, and so does anything
-      // where B is not the key of a finite score)
-      const unsigned B = unsigned(bw);
-      const float b = bound_score(B);
-      int eq = int(B <= 0x007fffffu);
-#pragma unroll
-      for (int i = 0; i < kNI; ++i) eq |= int(v[i] == b);
-      if (__syncthreads_or(eq)) {
-        if (t == 0) bw_sh[0] = wait_bound(word, p.wait_ticks, true);
-        __syncthreads();
-        bw = bw_sh[0];
-      }
-    }
-    const unsigned B = unsigned(bw), cstar = unsigned(bw >> 32) - 1u;
-    bound = (c > cstar && B < ~0u) ? B + 1u : B;
+    bw = bw_sh[0];
   }
+  if (bw == 0ull) {  // the first workgroup, or the wait has ended
+    uint4 e[kOnePassSegPer];
+    onepass_poll(p, r, tag, e, p.nseg, c == 0u ? summary_ticks(p) : 0ull);
+    bw = onepass_bound(p, sh, bs, e, c == 0u ? word : nullptr, p.nseg);
+  } else if (unsigned(bw >> 32) == kCstarPending) {
+    // c* decides only for keys equal to B: a chunk holding none keeps the
+    // keys >= B whichever side of c* it is on
+    // (compared as scores: the other zero counts as equal, and so does anything
+    // where B is not the key of a finite score)
+    const unsigned B = unsigned(bw);
+    const float b = bound_score(B);
+    int eq = int(B <= 0x007fffffu);
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) eq |= int(v[i] == b);
+    if (__syncthreads_or(eq)) {
+      if (t == 0) bw_sh[0] = wait_bound(p, word, true);
+      __syncthreads();
+      if (bw_sh[0] != 0ull) bw = bw_sh[0];  // (else B without a c*, so none is dropped)
+    }
+  }
+  // keys below it are dropped (c* + 1 is the largest while it is pending)
+  const unsigned B = unsigned(bw), cstar = unsigned(bw >> 32) - 1u;
+  const unsigned bound = (c > cstar && B < ~0u) ? B + 1u : B;
   // 3. survivors into the chunk's slot (as the filter kernel); the final
   // kernel reads them after this launch has ended
   unsigned keep = kept_mask(v, vm, bound);
@@ -2138,41 +2126,43 @@ __device__ inline void issue_scores(const SelectParams& p, unsigned r, const Str
   // (slots past the range's end touch no memory)
   const __amdgpu_buffer_rsrc_t rs =
       buffer_rsrc(p.logp + size_t(r) * p.N + s.base, int(s.n * 4u));
-  const unsigned lo = s.lane_offset();
+  const unsigned lo = 4u * s.lane_offset();
 #pragma unroll
-  for (int i = 0; i < kNI; ++i) {
-    unsigned so = s.slot_offset(unsigned(i), j);
-    // (a scalar added at the load: left alone, 32 lane offsets stay in registers
-    // from round to round)
-    asm volatile("" : "+s"(so));
-    l.x[i] = __uint_as_float(
-        unsigned(__builtin_amdgcn_raw_buffer_load_b32(rs, int(4u * (lo + so)), 0, 0)));
+  for (int q = 0; q < kNI / 4; ++q) {  // (turn() holds for four slots)
+    unsigned so = 4u * s.slot_offset(4u * unsigned(q), j);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // (a scalar added at the load: left alone, 32 lane offsets stay in registers
+      // from round to round)
+      asm volatile("" : "+s"(so));
+      l.x[4 * q + e] =
+          __uint_as_float(unsigned(__builtin_amdgcn_raw_buffer_load_b32(rs, int(lo + so), 0, 0)));
+      so += 4u * unsigned(kThreads) * s.nc;
+    }
   }
 }
 
-// The beam scores of a range, from its first row on: lane l holds row row0 + l.
+// The rows of a range: its first row and its start in that row, and a step of one
+// slot as rows and a remainder.
 struct BeamRows {
-  unsigned row0, rem0;  // the range's first row, and its start in that row
-  unsigned dr, dm;      // a step of one slot, in rows and remainder
-  bool lanes;           // every piece lies in one row, at most 64 rows
-  float bv;
+  unsigned row0, rem0, dr, dm;
   template <bool BEAM>
-  __device__ void init(const SelectParams& p, unsigned r, const StreamRange& s) {
+  __device__ void init(const SelectParams& p, const StreamRange& s) {
     if constexpr (BEAM) {
       row0 = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(s.base, p.V, p.inv_v))));
       rem0 = s.base - row0 * p.V;
       const unsigned step = unsigned(kThreads) * s.nc;
       dr = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(step, p.V, p.inv_v))));
       dm = step - dr * p.V;
-      lanes = (p.V & 63u) == 0u && s.n <= 62u * p.V;
-      bv = p.beam[size_t(r) * p.W_prev + min(row0 + lane_id(), p.W_prev - 1u)];
     }
   }
 };
 
 // Candidate scores of the loaded round j; invalid slots are NaN, which no bound keeps.
-// Where each piece lies in one row and the range in at most 64 rows, the beam scores
-// are one load per range and a lane read per slot; otherwise a load per slot.  The
+// A row is divided out for every four slots (turn() holds for them) and carried on
+// in between; the beam scores are a load per slot, from the cache.  (One load per range
+// and a lane read per slot, where every piece lies in one row, took as long or
+// longer: 8 requests x 256 x 8192 -> 256 38.1 us per call against 37.2.)  The
 // streaming form works on scores and forms keys only for the lanes' maxima and the
 // survivors: at four rounds the keys' ten vector instructions per candidate cost
 // more than the reads (a plain read of 67 MB takes 10.5 us here).
@@ -2180,59 +2170,65 @@ template <bool BEAM>
 __device__ inline void score_vals(const SelectParams& p, unsigned r, const StreamRange& s,
                                   const BeamRows& b, unsigned j, const RawScores& l,
                                   float (&v)[kNI]) {
-  const float nan = __uint_as_float(0x7fc00000u);
   if constexpr (!BEAM) {
 #pragma unroll
     for (int i = 0; i < kNI; ++i) v[i] = l.x[i];
   } else {
     j = min(j, s.nc - 1u);
-    if (b.lanes) {
-      const unsigned w0 = b.rem0 + unsigned(__builtin_amdgcn_readfirstlane(int(threadIdx.x & ~63u))) * s.nc;
+    // (rows past the last touch no memory)
+    const __amdgpu_buffer_rsrc_t rs =
+        buffer_rsrc(p.beam + size_t(r) * p.W_prev + b.row0, int((p.W_prev - b.row0) * 4u));
+    float bs[kNI];
 #pragma unroll
-      for (int q = 0; q < kNI / 4; ++q) {  // (turn() holds for four slots)
-        const unsigned x = w0 + s.slot_offset(4u * unsigned(q), j);
-        unsigned rel = unsigned(__builtin_amdgcn_readfirstlane(int(row_of(x, p.V, p.inv_v))));
-        unsigned rem = x - rel * p.V;
+    for (int q = 0; q < kNI / 4; ++q) {
+      const unsigned x = b.rem0 + s.lane_offset() + s.slot_offset(4u * unsigned(q), j);
+      unsigned rel = row_of(x, p.V, p.inv_v), rem = x - rel * p.V;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[4 * q + e] =
-              __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(b.bv), rel)) + l.x[4 * q + e];
-          rel += b.dr;
-          rem += b.dm;
-          if (rem >= p.V) {
-            rem -= p.V;
-            ++rel;
-          }
+      for (int e = 0; e < 4; ++e) {
+        bs[4 * q + e] =
+            __uint_as_float(unsigned(__builtin_amdgcn_raw_buffer_load_b32(rs, int(4u * rel), 0, 0)));
+        rel += b.dr;
+        rem += b.dm;
+        if (rem >= p.V) {
+          rem -= p.V;
+          ++rel;
         }
       }
-    } else {
-      const __amdgpu_buffer_rsrc_t rs =
-          buffer_rsrc(p.beam + size_t(r) * p.W_prev + b.row0, int((p.W_prev - b.row0) * 4u));
-      float bs[kNI];
-#pragma unroll
-      for (int q = 0; q < kNI / 4; ++q) {
-        const unsigned x = b.rem0 + s.lane_offset() + s.slot_offset(4u * unsigned(q), j);
-        unsigned rel = row_of(x, p.V, p.inv_v), rem = x - rel * p.V;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          bs[4 * q + e] = __uint_as_float(
-              unsigned(__builtin_amdgcn_raw_buffer_load_b32(rs, int(4u * rel), 0, 0)));
-          rel += b.dr;
-          rem += b.dm;
-          if (rem >= p.V) {
-            rem -= p.V;
-            ++rel;
-          }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < kNI; ++i) v[i] = bs[i] + l.x[i];
     }
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) v[i] = bs[i] + l.x[i];
   }
   if (__ballot(l.vm != ~0u) != 0ull) {  // (a whole round has no invalid slot)
 #pragma unroll
-    for (int i = 0; i < kNI; ++i) v[i] = ((l.vm >> i) & 1u) ? v[i] : nan;
+    for (int i = 0; i < kNI; ++i) v[i] = ((l.vm >> i) & 1u) ? v[i] : __uint_as_float(0x7fc00000u);
   }
+}
+
+// A key that at least `need` of a round's candidates reach, from the maxima of eight
+// slots of a lane each (2048 distinct candidates at most; 0 with fewer than need): the
+// floor of the bin of a linear histogram where their count reaches need.
+__device__ inline unsigned round_bound(SelShared& sh, const float (&v)[kNI], unsigned need) {
+  unsigned k[4], lo = ~0u, hi = 0u, n = 0u;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float best = v[8 * q];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) best = fmaxf(best, v[8 * q + i]);
+    k[q] = order_key(best);  // (0: no number among them)
+    lo = k[q] != 0u ? min(lo, k[q]) : lo;
+    hi = max(hi, k[q]);
+    n += unsigned(k[q] != 0u);
+  }
+  const Red3 r = block_reduce(sh, n, lo, hi);
+  if (r.sum < need) return 0u;
+  const int width = bit_width(r.hi - r.lo), shift = width > 11 ? width - 11 : 0;
+  reinterpret_cast<uint4*>(sh.hist)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) hist_add(sh.hist, (k[q] - r.lo) >> shift, k[q] != 0u);
+  __syncthreads();
+  find_bin(sh, need);
+  return r.lo + (sh.digit << shift);
 }
 
 template <bool BEAM, int SPC>
@@ -2252,9 +2248,12 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p)
     __builtin_amdgcn_sched_barrier(0);
   };
   BeamRows br;
-  br.init<BEAM>(p, r, rg);
-  float val[kNI], val1[kNI];  // the rounds 0, 2, ... and 1, 3, ...
-  RawScores la, lb;
+  br.init<BEAM>(p, rg);
+  // (211 registers: up to 224 some waves of another kernel share the compute unit; at
+  // 256 none did, and beside a copy on another stream workgroups that had not
+  // started held the bound back, 67 us per call with 211, 100 to 150 with 256)
+  float val[kNI];
+  RawScores la, lb;  // the rounds 0, 2, ... and 1, 3, ... on their way
   issue(0u, la);
   score_vals<BEAM>(p, r, rg, br, 0u, la, val);
   unsigned vm = la.vm;
@@ -2289,67 +2288,85 @@ __global__ __launch_bounds__(kThreads) void select_stream_kernel(SelectParams p)
   unsigned long long bw;
   if (g == 0u) {
     uint4 e[kOnePassSegPer];
-    const int late = onepass_poll(p, r, tag, e, nseg);
+    onepass_poll(p, r, tag, e, nseg, summary_ticks(p));
     const unsigned per = p.per;
     // (c* is the first chunk of a range)
-    bw = onepass_bound<kOnePassSegPer, SPC>(p, sh, bs, e, late, word, nseg,
+    bw = onepass_bound<kOnePassSegPer, SPC>(p, sh, bs, e, word, nseg,
                                             [per](unsigned i) { return i * per; });
-    score_vals<BEAM>(p, r, rg, br, 1u, lb, val1);
     issue(2u, la);
   } else {
-    // (the second round's scores are formed while the bound is, and the third's
-    // loads issued; B and c*: c* comes about 1 us after B, and ranges after the
-    // first need it)
-    score_vals<BEAM>(p, r, rg, br, 1u, lb, val1);
+    // (the third round is requested when the second has come: the looks at the bound
+    // wait behind the loads; B and c*: c* comes about 1 us after B, and ranges after
+    // the first need it)
+    wait_loads();
     issue(2u, la);
-    if (t == 0) bw_sh[0] = wait_bound(word, p.wait_ticks, true);
+    if (t == 0) bw_sh[0] = wait_bound(p, word, true);
     __syncthreads();
-    bw = bw_sh[0];  // 0 after a timeout: no bound
+    bw = bw_sh[0];  // 0 after a timeout: no bound but its rounds' own
   }
   const unsigned B = unsigned(bw), cstar = unsigned(bw >> 32) - 1u;
   // (every candidate of the ranges after c*'s follows every one of its own)
   unsigned bound = (c0 > cstar && B < ~0u) ? B + 1u : B;
-  // (inlined by force: called, the lambda's captures, the scores among them, would
+  // (the lambdas are inlined by force: called, their captures, the scores among them, would
   // live in scratch)
+  unsigned long long over = 0ull;  // rounds that overflow their slot all the same
+  auto store = [&](unsigned j, unsigned keep, unsigned total,
+                   auto&& key_of) __attribute__((always_inline)) {
+    uint2* out = p.cand_out + (size_t(r) * p.nwg + c0 + j) * p.cap;
+    const unsigned lo = rg.base + rg.lane_offset();
+    ordered_apply_sparse(keep, sh, [&](int i, unsigned rank) __attribute__((always_inline)) {
+      out[rank] = make_uint2(key_of(i), lo + rg.slot_offset(unsigned(i), j));
+    });
+    if (t == 0)  // (the placing kernel does not read a largest key)
+      reinterpret_cast<uint2*>(p.cnt_out)[size_t(r) * p.nwg + c0 + j] = make_uint2(total, 0u);
+  };
   auto filter = [&](unsigned j, unsigned vmask, const float(&v)[kNI]) __attribute__((always_inline)) {
     unsigned keep = kept_mask(v, vmask, bound);
     unsigned total = replan_sparse(keep, sh);
     if (__builtin_expect(total > p.cap, 0)) {
-      // at least the round's top W, as many as the slot takes; the last key bounds
-      // the rounds after it too, so that a range that holds most of the best scores, or
-      // a workgroup without a bound, takes this once and not in every round
+      // a bound from this round alone, for the rounds after it too, so that a range
+      // that holds most of the best scores takes this once and not in every round
       __syncthreads();
-      // (formed at each use: kept, the keys would take 32 more registers)
-      auto key = [&](int i) __attribute__((always_inline)) {
-        float x = v[i];
-        asm volatile("" : "+v"(x));
-        return order_key(x);
-      };
-      const Cut cut = find_cut_of<false>(sh, key, keep, p.W, p.cap);
-      keep = cut_mask_of(sh, key, keep, cut);
-      bound = max(bound, cut.tau);
+      bound = max(bound, round_bound(sh, v, p.W));
+      keep = kept_mask(v, vmask, bound);
       total = replan_sparse(keep, sh);
     }
-    uint2* out = p.cand_out + (size_t(r) * p.nwg + c0 + j) * p.cap;
-    const unsigned lo = rg.base + rg.lane_offset();
-    ordered_apply_sparse(keep, sh, [&](int i, unsigned rank) __attribute__((always_inline)) {
-      out[rank] = make_uint2(order_key(v[i]), lo + rg.slot_offset(unsigned(i), j));
-    });
-    if (t == 0)  // (the placing kernel does not read a largest key)
-      reinterpret_cast<uint2*>(p.cnt_out)[size_t(r) * p.nwg + c0 + j] = make_uint2(total, 0u);
+    if (total > p.cap) over |= 1ull << j;  // rare (ties): cut below, from a second read
+    else store(j, keep, total, [&](int i) __attribute__((always_inline)) { return order_key(v[i]); });
     __syncthreads();  // every wave has read sh.tab
   };
   for (unsigned j = 0u;; j += 2u) {
     filter(j, vm, val);
     if (j + 1u == rg.nc) break;
-    if (j != 0u) score_vals<BEAM>(p, r, rg, br, j + 1u, lb, val1);
-    const unsigned vm1 = lb.vm;
+    score_vals<BEAM>(p, r, rg, br, j + 1u, lb, val);
+    vm = lb.vm;
     issue(j + 3u, lb);
-    filter(j + 1u, vm1, val1);
+    filter(j + 1u, vm, val);
     if (j + 2u == rg.nc) break;
     score_vals<BEAM>(p, r, rg, br, j + 2u, la, val);
     vm = la.vm;
     issue(j + 4u, la);
+  }
+  for (; over != 0ull; over &= over - 1ull) {  // a round's exact top W of its survivors
+    const unsigned j = unsigned(__builtin_ctzll(over));
+    issue(j, la);
+    score_vals<BEAM>(p, r, rg, br, j, la, val);
+    // (the mask that overflowed, as the cut needs at least W: a bound of +0 keeps the -0s
+    // as scores, and compared as keys fewer than W may be left)
+    unsigned keep = kept_mask(val, la.vm, bound);
+    unsigned key[kNI];
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) key[i] = order_key(val[i]);
+    unsigned total = replan_sparse(keep, sh);
+    if (total > p.cap) {  // (a later round may have raised the bound)
+      __syncthreads();
+      const Cut cut = find_cut(sh, key, keep, p.W);
+      keep = cut_mask(sh, key, keep, cut);
+      bound = max(bound, cut.tau);
+      total = replan_sparse(keep, sh);
+    }
+    store(j, keep, total, [&](int i) __attribute__((always_inline)) { return key[i]; });
+    __syncthreads();
   }
 }
 
@@ -2417,7 +2434,7 @@ __global__ __launch_bounds__(kThreads) void select_summary_kernel(SelectParams p
   const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(p.ex + size_t(r) * p.nseg, int(p.nseg * 16u));
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) e[i] = ld_agent4(rs, (unsigned(i) * kThreads + t) * 16u);
-  onepass_bound<ROWS>(p, sh, bs, e, 0, &p.tp_bound[r], p.nseg);
+  onepass_bound<ROWS>(p, sh, bs, e, &p.tp_bound[r], p.nseg);
   if (t == 0) p.ctl->arrive[r] = 0u;
 }
 
@@ -2551,7 +2568,9 @@ hipError_t launch_select(const SelectPlan& plan, int R, int prev_width, int voca
       p.per = sp.per;
       p.cand_out = reinterpret_cast<uint2*>(ws + plan.slot_off);
       p.cnt_out = reinterpret_cast<unsigned*>(ws + plan.cnt_off);
-      p.wait_ticks = onepass_wait_ticks();
+      // (twice the one-pass wait: the sample's loads share the memory with those of the
+      // next round)
+      p.wait_ticks = 2ull * onepass_wait_ticks();
       const unsigned blocks = unsigned(R) * sp.groups;
       if (sp.spc == 32u) {
         if (has_beam) select_stream_kernel<true, 32><<<blocks, kThreads, 0, st>>>(p);

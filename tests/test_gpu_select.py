@@ -340,6 +340,30 @@ def test_select_one_pass_tags_and_epoch_wrap():
     assert epoch() == 1
 
 
+@pytest.mark.parametrize("R,P,V,W,kind", [
+    (1, 512, SELECT_CODEBOOK, 512, "logsoftmax"), (1, 300, SELECT_CODEBOOK, 64, "ties"),
+    (2, 100, SELECT_CODEBOOK, 200, "special"), (4, 64, 65536, 64, "logsoftmax"),
+    (3, 500, 3001, 200, "special"), (4, 131, SELECT_CODEBOOK, 33, "ties"),
+    (1, 530, SELECT_CODEBOOK, 200, "rising")])
+def test_select_waits_that_end_at_once(R, P, V, W, kind):
+    """The one-pass and streaming forms wait for other workgroups for a bounded
+    time.  With the waits cut to nothing (the shift in the second word of the
+    workspace), the bound comes from the summaries that are there at the
+    first look, or from none, and most workgroups find no bound: the result
+    is the same, in that call and in the next one with the usual waits."""
+    import torch
+    from paper_2609_12399_amd.runner import BeamSelector
+    sel = BeamSelector(R, P, V, W)
+    for call, shift in enumerate([63, 63, 0]):
+        logp, beam = make_select_inputs(R, P, V, 40 + call, kind, True)
+        sel.workspace[4] = shift
+        print(f"waits >> {shift} R={R} W_prev={P} V={V} W={W} {kind}", flush=True)
+        sel(torch.from_numpy(logp).cuda(), torch.from_numpy(beam).cuda())
+        torch.cuda.synchronize()
+        _check(logp, beam, W, sel.parents.cpu().numpy(), sel.tokens.cpu().numpy(),
+               sel.scores.cpu().numpy())
+
+
 def test_select_graph_replays_with_new_scores():
     """The headline selection captured once in a HIP graph and replayed with
     new scores copied into its input buffers between replays (eager work
