@@ -795,12 +795,18 @@ struct Swz {
   }
 };
 
+// The operands of two chunks.  The two chunks' keys come first and next to each other,
+// so that (up to d_k = 256) both are reached from one lane address and a constant, as
+// are the other pairs.  With one struct per chunk every address was held twice, and the
+// compiler spilled 46 registers of a lane at d_k = 256 and 3 at 128 (now 16 and none;
+// T' read late at 256, see kLateT): 7 chunks of 8 heads of 256 62 -> 54 us per call, 16 x 8
+// heads x 1000 tokens 171 -> 139.
 template <int DK, int NW>
-struct ScanBuf {
-  uint4 T[kTChunk];
-  alignas(16) Swz<DK> K;
-  alignas(16) Swz<16 * NW> V;
-  alignas(16) float gam[kC];
+struct ScanBufs {
+  alignas(16) Swz<DK> K[2];
+  alignas(16) Swz<16 * NW> V[2];
+  uint4 T[2][kTChunk];
+  alignas(16) float gam[2][kC];
 };
 
 // The scan over the chunks of one segment of one (request, value head): wave w
@@ -832,7 +838,7 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
   constexpr int PS = NB / 2 < 4 ? NB / 2 : 4;
   auto t0 = [](int h) constexpr { return h / PS * (2 * PS) + h % PS; };
   constexpr int NK = kC * DK / 8 / TH, NT = (kTChunk + TH - 1) / TH, NV = 2;
-  __shared__ __align__(16) ScanBuf<DK, NW> buf[2];
+  __shared__ __align__(16) ScanBufs<DK, NW> buf;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lq = lane >> 4;
@@ -907,23 +913,23 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
       rt[q] = __builtin_amdgcn_raw_buffer_load_b128(tr, tid * 16, q * TH * 16, 0);
     rg = p.gam[cu * kC + (tid & 63)];
   };
-  auto store = [&](ScanBuf<DK, NW>& s) {
+  auto store = [&](int x) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < NK; ++q) {
       const int e = tid + q * TH;
-      s.K.put(e / (DK / 8), e % (DK / 8), rk[q]);
+      buf.K[x].put(e / (DK / 8), e % (DK / 8), rk[q]);
     }
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
       const int e = tid + q * TH;
-      s.V.put(e / (2 * NW), e % (2 * NW), rv[q]);
+      buf.V[x].put(e / (2 * NW), e % (2 * NW), rv[q]);
     }
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
       const int e = tid + q * TH;
-      if (kTChunk % TH == 0 || e < kTChunk) *reinterpret_cast<u32x4*>(&s.T[e]) = rt[q];
+      if (kTChunk % TH == 0 || e < kTChunk) *reinterpret_cast<u32x4*>(&buf.T[x][e]) = rt[q];
     }
-    if (tid < kC) s.gam[tid] = rg;
+    if (tid < kC) buf.gam[x][tid] = rg;
   };
   // this lane's LDS offsets: key pieces of row lr from piece lq; transposed
   // keys and values, row 4 lq + lr / 4 from piece lr % 4
@@ -935,7 +941,11 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
   // scheduling barriers keep them there), and within a phase the products and
   // the vector work that prepares the next operands are independent, so that
   // the matrix core and the vector unit run together.
-  auto step = [&](const ScanBuf<DK, NW>& s) {
+  auto step = [&](int x) __attribute__((always_inline)) {
+    const Swz<DK>& sK = buf.K[x];
+    const Swz<16 * NW>& sV = buf.V[x];
+    const uint4* const sT = buf.T[x];
+    const float* const sgam = buf.gam[x];
     f32x4 yh[4], yl[4];
 #pragma unroll
     for (int a = 0; a < 4; ++a) yh[a] = yl[a] = z;
@@ -943,7 +953,7 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
     auto read_k = [&](int h, uint4(&f)[4]) {
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        const char* const k = s.K.template at<char>(kb, t0(h), KR * a);
+        const char* const k = sK.template at<char>(kb, t0(h), KR * a);
         const uint2 k0 = *reinterpret_cast<const uint2*>(k),
                     k1 = *reinterpret_cast<const uint2*>(k + 32 * PS);
         f[a] = make_uint4(k0.x, k0.y, k1.x, k1.y);
@@ -952,6 +962,15 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
     uint2 v[4];
     f32x4 g[4];
     uint4 tf[4][3];
+    // (at d_k = 256 T' is read when its product comes: read ahead, as for fewer columns,
+    // 27 registers of a lane spill in place of 16, 7 chunks of 8 heads 60 us against 54)
+    constexpr bool kLateT = NB > 8;
+    auto read_tf = [&]() {
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) tf[a][q] = sT[(3 * (a < 2 ? a : 2 * a - 2) + q) * 64 + lane];
+    };
     read_k(0, kf[0]);
     cut3(st[t0(0)], st[t0(0) + PS], sh[0], sm[0], sl[0]);
 #pragma unroll
@@ -962,24 +981,21 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
       } else {
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          v[a] = lds_tr4(s.V.template at<uint16_t>(vb, 0, VR * a));
-          g[a] = *reinterpret_cast<const f32x4*>(&s.gam[16 * a + 4 * lq]);
+          v[a] = lds_tr4(sV.template at<uint16_t>(vb, 0, VR * a));
+          g[a] = *reinterpret_cast<const f32x4*>(&sgam[16 * a + 4 * lq]);
         }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int q = 0; q < 3; ++q) tf[a][q] = s.T[(3 * (a < 2 ? a : 2 * a - 2) + q) * 64 + lane];
+        if constexpr (!kLateT) read_tf();
       }
       __builtin_amdgcn_sched_barrier(0);
-      const int x = h & 1;
+      const int e = h & 1;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) yl[a] = mfma_bf16(kf[x][a], sl[x], yl[a]);
+      for (int a = 0; a < 4; ++a) yl[a] = mfma_bf16(kf[e][a], sl[e], yl[a]);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) yh[a] = mfma_bf16(kf[x][a], sh[x], yh[a]);
+      for (int a = 0; a < 4; ++a) yh[a] = mfma_bf16(kf[e][a], sh[e], yh[a]);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) yl[a] = mfma_bf16(kf[x][a], sm[x], yl[a]);
+      for (int a = 0; a < 4; ++a) yl[a] = mfma_bf16(kf[e][a], sm[e], yl[a]);
       if (h + 1 < DK / 32)
-        cut3(st[t0(h + 1)], st[t0(h + 1) + PS], sh[x ^ 1], sm[x ^ 1], sl[x ^ 1]);
+        cut3(st[t0(h + 1)], st[t0(h + 1) + PS], sh[e ^ 1], sm[e ^ 1], sl[e ^ 1]);
     }
     __builtin_amdgcn_sched_barrier(0);
     // D0(t = 16 a + 4 lq + i, n = lr) = V - gamma_t Y
@@ -994,12 +1010,16 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
     };
     uint4 dh[2], dm[2], dl[2], tg[2][3];
     f32x4 eh[4], el[4];
+    if constexpr (kLateT) read_tf();
     // D' = T' D0: the first 32 tokens' products beside the split of the others
+    auto read_tg = [&]() {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      tg[0][q] = s.T[(3 * 3 + q) * 64 + lane];
-      tg[1][q] = s.T[(3 * 5 + q) * 64 + lane];
-    }
+      for (int q = 0; q < 3; ++q) {
+        tg[0][q] = sT[(3 * 3 + q) * 64 + lane];
+        tg[1][q] = sT[(3 * 5 + q) * 64 + lane];
+      }
+    };
+    if constexpr (!kLateT) read_tg();
     split3(d0(0), d0(1), dh[0], dm[0], dl[0]);
     __builtin_amdgcn_sched_barrier(0);
     // part by part over the tiles, so that no product waits for the one before
@@ -1020,6 +1040,7 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
     apply(tf, 0, 0, 4);
     split3(d0(2), d0(3), dh[1], dm[1], dl[1]);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kLateT) read_tg();
     // state tiles per group of the update (four at d_k = 256: with eight the
     // operands do not fit in the registers, 242 -> 162 us at 4 x 8 heads x 2048 tokens)
     constexpr int NG = NB < 8 ? NB : NB == 8 ? 8 : 4;
@@ -1029,13 +1050,13 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
       for (int b = 0; b < NG; ++b)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const uint2 k0 = lds_tr4(s.K.template at<uint16_t>(tb, b0 + b, 2 * KR * h)),
-                      k1 = lds_tr4(s.K.template at<uint16_t>(tb, b0 + b, 2 * KR * h + KR));
+          const uint2 k0 = lds_tr4(sK.template at<uint16_t>(tb, b0 + b, 2 * KR * h)),
+                      k1 = lds_tr4(sK.template at<uint16_t>(tb, b0 + b, 2 * KR * h + KR));
           kt[b][h] = make_uint4(k0.x, k0.y, k1.x, k1.y);
         }
     };
     read_t(0);
-    const float gc = s.gam[kC - 1];
+    const float gc = sgam[kC - 1];
     __builtin_amdgcn_sched_barrier(0);
     uint4 ph[2], pm[2], pl[2];  // D' of the two token halves, split
     apply(tg, 1, 2, 2);
@@ -1072,22 +1093,22 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
   if (cb < ce) {  // (an empty prompt has no chunk: S = 0)
     // (the scheduling barriers keep the requests ahead of the step: left alone,
     // the compiler sinks them to its end and the next store waits for memory)
-    auto turn = [&](int c, const ScanBuf<DK, NW>& now, ScanBuf<DK, NW>& next) {
-      store(next);
+    auto turn = [&](int c, int x) __attribute__((always_inline)) {
+      store(x ^ 1);
       __builtin_amdgcn_sched_barrier(0);
       load(c + 2);
       __builtin_amdgcn_sched_barrier(0);
-      step(now);
+      step(x);
       __syncthreads();
     };
     load(cb);
-    store(buf[0]);
+    store(0);
     load(cb + 1);
     __syncthreads();
     for (int c = cb; c < ce; c += 2) {
-      turn(c, buf[0], buf[1]);
+      turn(c, 0);
       if (c + 1 == ce) break;
-      turn(c + 1, buf[1], buf[0]);
+      turn(c + 1, 1);
     }
   }
   if (ident) {
@@ -1095,7 +1116,7 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
     // three bf16 parts: through LDS (whose last reader passed the barrier
     // above, or there was none), a wave per 16 columns of A
     constexpr int LD = DK + 4;
-    float* const x = reinterpret_cast<float*>(buf);
+    float* const x = reinterpret_cast<float*>(&buf);
     static_assert(sizeof(buf) >= sizeof(float) * 16 * NW * LD, "A's rows fit the operand buffers");
 #pragma unroll
     for (int b = 0; b < NB; ++b)
