@@ -83,26 +83,38 @@ size_t prefill_chunked_workspace_bytes(const Shape& s, int prompt_len) {
 
 // A scan workgroup holds up to 128 rows of the state (or of a segment's d_k x d_k
 // transition matrix) for the whole segment, one workgroup per compute unit (two
-// at d_k <= 64, by their LDS).  A chunk takes about 4 us there, the launch that
-// chains n segments about 4 + 1.5 (n - 1) us (both measured at 16 heads, d = 128),
-// and every segment but the first also carries its transition matrix, so segments
-// pay only while workgroups are missing: 16 heads x 64 chunks 8 segments, 42 + 12 us
-// (4: 66 + 7; 6: 51 + 10); 64 heads x 32 chunks 2, 75 + 8 (4: 83 + 14); 256 heads none.
+// at d_k <= 64, by their LDS; each then takes about a quarter longer).  Every segment but
+// the first also carries its transition matrix, so segments pay only while workgroups
+// are missing.  The launch that chains them reads those matrices in every workgroup of 16
+// state rows, and the segments' states are written and read once more.  The times
+// below fit all of 103 shapes and segment counts timed (8 to 64 heads, 2 to 64 chunks): the
+// count taken is at most 5% slower than the fastest.  In us per call: 16 heads of 128,
+// 64 chunks 8 segments 60 (4: 80; 1: 233), 7 chunks 4 segments 24.6 (1: 35.1); 8 heads of
+// 256, 7 chunks 2 segments 44.9 (1: 53.4), 5 chunks none 42.5; 32 heads of 256 x 512, 16
+// chunks none 110 (2: 146; 4: 172).
 int prefill_segments(const Shape& s, int nch) {
-  if (nch < 8 || s.cus <= 0) return 1;
+  if (nch < 4 || s.cus <= 0) return 1;
   const size_t waves = std::min(s.dv / 16, 8);
   const size_t gb = s.dv / (16 * waves), ga = s.dk / (16 * waves);
-  const size_t units = size_t(s.R) * s.HV;
-  const size_t slots = size_t(s.cus) * (s.dk <= 64 ? 2 : 1);
+  const size_t units = size_t(s.R) * s.HV, cus = size_t(s.cus);
+  const size_t slots = cus * (s.dk <= 64 ? 2 : 1);
   const size_t room = size_t(nch) * (size_t(kPrefillChunk) * (2 * s.dk + s.dv) * sizeof(float) -
                                      kPrefillFactorBytes);
-  auto cost = [&](int n, int chunks) {  // in 0.4 us
+  // ns per chunk of the scan, and per chained segment
+  const size_t chunk_ns = s.dk == 32 ? 1600 : s.dk == 64 ? 2250 : s.dk == 128 ? 3500 : 5700;
+  const size_t chain_ns = s.dk == 32 ? 450 : s.dk == 64 ? 1000 : s.dk == 128 ? 1400 : 4600;
+  const size_t chainers = std::max(units * size_t(s.dv / 16), size_t(192));
+  auto cost = [&](int n, int chunks) {
     const size_t wgs = units * (gb + size_t(n - 1) * (gb + ga));
-    return 10 * ((wgs + slots - 1) / slots) * size_t(chunks) + (n > 1 ? 10 + 4 * size_t(n - 1) : 0);
+    const size_t scan = (wgs + slots - 1) / slots * size_t(chunks) * chunk_ns;
+    if (n == 1) return scan;
+    return (s.dk <= 64 && wgs > cus ? scan * 5 / 4 : scan) + 2000 +
+           chain_ns * size_t(n - 1) * chainers / 192 +
+           size_t(n) * units * s.dv * s.dk * 8 / 5000 /* bytes at 5 TB/s */;
   };
   int best = 1;
   size_t best_cost = cost(1, nch);
-  for (int want = 2; want <= nch / 4 && want <= 16; ++want) {
+  for (int want = 2; want <= nch / 2 && want <= 16; ++want) {
     const int cps = (nch + want - 1) / want, n = (nch + cps - 1) / cps;
     // the segments' B (fp32) and A (three bf16 parts) stay inside the workspace
     if ((size_t(n) * s.dv * 4 + size_t(n - 1) * s.dk * 6) * s.dk > room) continue;

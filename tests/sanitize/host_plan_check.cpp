@@ -54,11 +54,11 @@ static void configs() {
                   EXPECT(!s.borrow || (l.k == 0 && l.v == 0 && l.ab == 0));
                   EXPECT(s.delta == (l.d > 0));
                   EXPECT(prefill_chunked_workspace_bytes(s, 0) % 256 == 0);
-                  for (int nch : {0, 1, 7, 8, 9, 31, 64, 129, 1000}) {
+                  for (int nch : {0, 1, 3, 4, 5, 7, 8, 9, 31, 64, 129, 1000}) {
                     Shape g = s;
                     g.cus = 256;
                     const int n = prefill_segments(g, nch);
-                    EXPECT(n == 1 || (n > 1 && n <= nch / 4));
+                    EXPECT(n == 1 || (n > 1 && n <= nch / 2 && n <= 16));
                     // factors, the segments' B (fp32) and A (three bf16 parts)
                     const size_t units = size_t(s.R) * s.HV;
                     const size_t seg = n == 1 ? 0 : (size_t(n) * s.dv * 4 + size_t(n - 1) * s.dk * 6) * s.dk;
@@ -70,6 +70,30 @@ static void configs() {
                 }
   EXPECT(ok > 0);
   EXPECT(shape_of(nullptr, nullptr) == ONELA_EINVAL);
+}
+
+// Prompts cut where the timed shapes say so (256 compute units): heads of 256 from six
+// chunks on, and not where the chaining costs more than the idle part of the chip.
+static void segments() {
+  auto cut = [](int R, int HV, int dk, int dv, int nch) {
+    Shape s{};
+    s.R = R;
+    s.HK = s.HV = HV;
+    s.dk = dk;
+    s.dv = dv;
+    s.bf16 = true;
+    s.cus = 256;
+    return prefill_segments(s, nch);
+  };
+  EXPECT(cut(1, 8, 256, 256, 5) == 1);
+  EXPECT(cut(1, 8, 256, 256, 6) == 2);
+  EXPECT(cut(1, 8, 256, 256, 7) == 2);
+  EXPECT(cut(1, 8, 256, 512, 7) == 2);
+  EXPECT(cut(1, 8, 256, 256, 32) == 8);
+  EXPECT(cut(4, 8, 256, 512, 16) == 1);
+  EXPECT(cut(1, 16, 128, 128, 64) == 8);
+  EXPECT(cut(1, 16, 64, 64, 64) == 8);
+  EXPECT(cut(16, 16, 128, 128, 16) == 1);
 }
 
 static void select_plans() {
@@ -163,6 +187,7 @@ static void protocol_walk() {
 
 int main() {
   configs();
+  segments();
   select_plans();
   protocol_walk();
   if (failures) {

@@ -110,7 +110,7 @@ def test_chunked_matches_sequential_prefill():
     assert state_err(got, seq.astype(np.float64)) <= TOL
 
 
-# bf16 keys: the scan cut into segments (few heads, from 8 chunks on), with the
+# bf16 keys: the scan cut into segments (few heads, from 4 chunks on), with the
 # last segment shorter, a ragged last chunk, unit counts on and off the
 # XCD-aware order, and one case each side of the cut.  Bar: every chunk rounds
 # the state a few times at 2^-24 of its largest element and later chunks only
@@ -119,7 +119,10 @@ def test_chunked_matches_sequential_prefill():
 @pytest.mark.parametrize("HK,HV,dk,dv,P", [
     (1, 3, 128, 128, 64 * 9 + 17), (2, 8, 128, 128, 64 * 8), (2, 2, 128, 128, 64 * 7 + 1),
     (1, 2, 64, 64, 64 * 33 + 5), (1, 1, 32, 32, 64 * 12), (1, 3, 128, 512, 64 * 11 + 63),
-    (2, 2, 256, 256, 64 * 17 + 2), (1, 2, 256, 512, 64 * 9), (4, 8, 128, 256, 64 * 20 + 30)])
+    (2, 2, 256, 256, 64 * 17 + 2), (1, 2, 256, 512, 64 * 9), (4, 8, 128, 256, 64 * 20 + 30),
+    # segments of two and three chunks, the shortest cut; 32 and 64 with 16 segments
+    (2, 2, 256, 256, 64 * 6 + 5), (1, 2, 256, 512, 64 * 6), (2, 2, 128, 128, 64 * 4),
+    (1, 4, 64, 64, 64 * 4 + 1), (1, 1, 32, 32, 64 * 32 - 9), (1, 2, 64, 64, 64 * 63 + 1)])
 def test_chunked_prefill_segments(HK, HV, dk, dv, P):
     spec = W.WorkloadSpec(f"pfs_{dk}_{dv}", 1, HK, HV, dk, dv, P, (8,), "bf16", "uniform",
                           alpha_mu=-5.0, seed=P)
