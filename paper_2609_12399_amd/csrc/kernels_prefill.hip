@@ -125,7 +125,7 @@ struct P1Shared {
   float T[kC][kC + 4];    // (I + M)^{-1}
   union {
     float M[kC][kC + 4];  // until T is formed
-    float X[kC][128 + 4]; // then a 128-column block of beta V
+    float X[kC][128 + 4]; // then beta V (d_v <= 128)
   };
   float P[7][kC];         // P[k][t]: product of the 2^k decays ending at token t
   alignas(16) float be[kC], gam[kC], sig[kC];
@@ -279,28 +279,25 @@ __global__ __launch_bounds__(kP1Threads) void prefill_chunk_kernel(PrefillParams
   // token tile a) of lane l holds U'^T(16 rb + l % 16, t = 16 a + 4 (l / 16) + j),
   // j = 0..3
   f32x4* udst = reinterpret_cast<f32x4*>(p.utb + cu * DV * kC);
-  constexpr int VC = DV < 128 ? DV : 128;  // V columns per block
-  constexpr int NBU = VC / 16;
-  for (int cb = 0; cb < DV; cb += VC) {
-    fill_rows<VC, 128 + 4>(&sh.X[0][0], p.v, n, cb,
-                             [&](int t) { return ((tok0 + t) * p.HV + hv) * DV; },
-                             [&](int t) { return sh.be[t]; });
-    __syncthreads();
-    for (int x = w; x < 4 * NBU; x += 4) {
-      const int a = x / NBU, b = x - a * NBU;
-      f32x4 acc4[4] = {};
-      for (int ks = 0; ks < 4 * (a + 1); ks += 4) {
+  static_assert(DV <= 128, "beta V takes M's place in one piece");
+  constexpr int NBU = DV / 16;
+  fill_rows<DV, 128 + 4>(&sh.X[0][0], p.v, n, 0,
+                         [&](int t) { return ((tok0 + t) * p.HV + hv) * DV; },
+                         [&](int t) { return sh.be[t]; });
+  __syncthreads();
+  for (int x = w; x < 4 * NBU; x += 4) {
+    const int a = x / NBU, b = x - a * NBU;
+    f32x4 acc4[4] = {};
+    for (int ks = 0; ks < 4 * (a + 1); ks += 4) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int kk = 4 * (ks + u) + l4;
-          acc4[u] = mfma4(sh.T[16 * a + l16][kk], sh.X[kk][16 * b + l16], acc4[u]);
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int kk = 4 * (ks + u) + l4;
+        acc4[u] = mfma4(sh.T[16 * a + l16][kk], sh.X[kk][16 * b + l16], acc4[u]);
       }
-      const f32x4 acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
-      const f32x4 sg = *reinterpret_cast<const f32x4*>(&sh.sig[16 * a + 4 * l4]);
-      udst[((cb / 16 + b) * 4 + a) * 64 + lane] = sg * acc;
     }
-    __syncthreads();
+    const f32x4 acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
+    const f32x4 sg = *reinterpret_cast<const f32x4*>(&sh.sig[16 * a + 4 * l4]);
+    udst[(b * 4 + a) * 64 + lane] = sg * acc;
   }
   if (tid < 16) p.gb[cu * 16 + tid] = sh.gam[kC - 1];
 }
@@ -318,20 +315,15 @@ template <int N>
 struct Vec {
   typedef float type __attribute__((ext_vector_type(N)));
 };
-template <>
-struct Vec<1> {
-  typedef float type;
-};
 
 // Components N g .. N g + N - 1 of v.
 template <int N>
 __device__ inline typename Vec<N>::type slice(const f32x4& v, int g) {
+  static_assert(N == 4 || N == 2, "d_k <= 128");
   if constexpr (N == 4) {
     return v;
-  } else if constexpr (N == 2) {
-    return g == 0 ? v.xy : v.zw;
   } else {
-    return v[g];
+    return g == 0 ? v.xy : v.zw;
   }
 }
 
@@ -545,8 +537,8 @@ __device__ inline float row_shift1(float x) {
 // and T' = diag(sigma) (I + M)^{-1} diag(beta), split into three bf16 parts, in
 // the order the scan's lanes load it as an MFMA A operand.  Four waves.
 //   Bound: latency of its serial steps (one dependent chain per chunk); the
-// workgroup holds 36 KB of LDS at d_k = 128, so four of them share a compute
-// unit and hide each other's chain.  The inverse is formed by 16-token blocks:
+// workgroup holds 36 KB of LDS up to d_k = 128, so four of them share a compute
+// unit (52 KB and three at 256) and hide each other's chain.  The inverse is formed by 16-token blocks:
 // the four diagonal blocks by forward substitution, one per wave with a column
 // per lane (16 dependent steps instead of 64), then each wave the blocks below
 // the diagonal block of its block column, T_ij = -T_ii sum_k M_ik T_kj, on
@@ -556,7 +548,7 @@ __device__ inline float row_shift1(float x) {
 // the diagonal tiles, down the tile's rows (looked up in a table of doubled
 // products, each waited for by itself, the launch took 51 us at 16 x 16 heads x 16 chunks).
 template <int DK>
-__global__ __launch_bounds__(kP1Threads, 4) void prefill_factor_kernel(PrefillParams p) {
+__global__ __launch_bounds__(kP1Threads, DK == 256 ? 3 : 4) void prefill_factor_kernel(PrefillParams p) {
   using Sh = FactorShared<DK>;
   __shared__ __align__(16) Sh sh;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1042,7 +1034,8 @@ __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(Prefi
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (kLateT) read_tg();
     // state tiles per group of the update (four at d_k = 256: with eight the
-    // operands do not fit in the registers, 242 -> 162 us at 4 x 8 heads x 2048 tokens)
+    // operands do not fit in the registers, 242 us against 162 at 4 x 8 heads x 2048 tokens
+    // when it was chosen, 134 now)
     constexpr int NG = NB < 8 ? NB : NB == 8 ? 8 : 4;
     uint4 kt[NG][2];
     auto read_t = [&](int b0) {
