@@ -25,8 +25,8 @@
 //     where the chip would otherwise be idle;
 //   prefill_combine_kernel: chains the segments (only with more than one).
 // Measured (one MI355X, 16 heads, d = 128; the launches by rocprofv3): 4096 tokens
-// factors 13 us, scan 42, combination 11, against 57 + 98 for the two launches of the
-// form below; 16 requests x 1000 tokens 36 + 80 against 229 + 207.
+// factors 13 us, scan 41, combination 11, against 57 + 98 for the two launches of the
+// form below; 16 requests x 1000 tokens 36 + 78 against 229 + 207.
 //
 // fp32 keys and values:
 //   prefill_chunk_kernel: one workgroup per (request, value head, chunk) forms T
@@ -820,6 +820,10 @@ struct ScanBufs {
 // eight waves share them; the next chunk's operands travel in registers from
 // global memory (requested one chunk ahead) to the other LDS buffer, one barrier
 // per chunk.
+//   Bound: no one unit.  At 16 requests x 16 heads x 1000 tokens (78 us) the matrix cores are
+// busy 38% of the time and the vector units with other instructions about 35%; a wave
+// waits 27% of its cycles (LDS, the barrier) and is ready but not issued 36%, with two
+// waves per SIMD.
 template <int DK, int DV>
 __global__ __launch_bounds__(64 * kScanWaves<DV>) void prefill_scan_kernel(PrefillParams p) {
   constexpr int NW = kScanWaves<DV>, TH = 64 * NW;

@@ -2072,10 +2072,10 @@ __global__ __launch_bounds__(kThreads) void select_onepass_kernel(SelectParams p
 // 256 with steeply rising beam scores 101 (now 66; two passes: 76).
 //   Bound: the first round's round trip and the bound (about 12 us), then per
 // round a barrier-separated compaction by one workgroup per compute unit (8 x 256 x
-// 8192, 67 MB in four rounds per workgroup: 31.6 us; a plain read takes 10.5).  With
-// keys in place of scores 34.5 us; three rounds ahead in place of two 38 us (the
-// polls of the bound wait behind the loads: the vector memory counter retires in
-// order).
+// 8192, 67 MB in four rounds per workgroup: 30.9 us; a plain read takes 10.5).
+// Measured with whole chunks as rounds, then 31.6 us: with keys in place of scores
+// 34.5; three rounds ahead in place of two 38 (the polls of the bound wait behind the
+// loads: the vector memory counter retires in order).
 
 // The range of a workgroup, [base, base + n) of its request, and its rounds.  It is cut
 // into pieces of 64 candidates, and these into rows of nc pieces, row 8 i + w for slot
@@ -2487,14 +2487,17 @@ OnePassDevice onepass_device() {
 }
 unsigned onepass_capacity() { return onepass_device().capacity; }
 
-// Workgroups per request of the streaming form, and the segments of a chunk
-// that have summaries; 0 when the call is not for it.  Measured against the two
-// passes (wave maxima or summaries, then the filter; us per launch, with the placing
-// launch): 8 requests x 256 x 8192 -> 256 31.6 + 6.5 against 22.3 + 22.3 + 4.8; 4 x 256 x
-// 8192 20.8 + 4.6 against 9.1 + 19.2 + 4.0; 2 x 512 x 8192 -> 512 20.8 + 6.7 against
-// 9.0 + 19.6 + 4.6.  With more expected survivors than kStreamKeep the placing
-// takes longer than the pass saves: 1024 x 8192 -> 1024 (2800 expected) 21.8 + 55.6
-// against 9.0 + 21.0 + 7.1; 16 x 256 x 8192 -> 256 (2840) 66 + 37 against 38 + 43 + 6.
+// Workgroups per request of the streaming form, and the segments of a round
+// that have summaries; 0 when the call is not for it.  Measured per call against the
+// two passes (wave maxima or summaries, then the filter): 8 requests x 256 x 8192 -> 256
+// 37.3 us against 48.7, with 8191 tokens 36.3 against 48.8, with tokens sorted by frequency
+// 42.8 against 54.7, with rising beam scores 56.7 against 76.2; 4 x 256 x 8192 22.1 against
+// 29.7; 2 x 512 x 8192 -> 512 24.6 against 30.8 (tied scores 30.6 against 31.3); 3 x 5000 x
+// 300 -> 128 22.4 against 35.4; 60 x 100 x 8000 -> 16 (13 rounds) 64.9 against 105.
+// With more expected survivors than kStreamKeep (measured with whole chunks as rounds and
+// 4096 staged survivors) the placing takes longer than the pass saves: launches of 1024 x
+// 8192 -> 1024 (2800 expected) 21.8 + 55.6 us against 9.0 + 21.0 + 7.1; 16 x 256 x 8192 ->
+// 256 (2840) 66 + 37 against 38 + 43 + 6.
 struct StreamPlan {
   unsigned groups, per, spc;
 };

@@ -37,7 +37,16 @@ DECODE_RE = re.compile(r"decode_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (true|
                        r"(true|false)(?:, (true|false))?>")
 
 
+REPLAY_RE = re.compile(r"replay_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (true|false), "
+                       r"(true|false)>")
+
+
 def short_name(name: str) -> str:
+    m = REPLAY_RE.search(name)
+    if m:
+        dk, _, _, _, chain, bf16, fused = m.groups()
+        return (f"replay_kernel<{'fused' if fused == 'true' else 'decode'}, d={dk}, chain={chain}, "
+                f"{'bf16' if bf16 == 'true' else 'f32'}>")
     m = DECODE_RE.search(name)
     if m:
         dk, dv, mb, nblk, chain, bf16, fused, borrow = m.groups()
